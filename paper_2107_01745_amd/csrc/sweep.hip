@@ -398,7 +398,7 @@ __device__ void bwd_node(const SweepArgs &a, const InstDesc &I, int i, const Wav
     zero(kacc);
     zero(qacc);
     if constexpr (CH == 1) {
-        if (nx <= G && nu >= 2) {
+        if (nx <= G && nu <= G && nu >= 2) {   // both products at most G columns wide
             gemv_pairs<NRHS, G, RB>(a.Rn + I.Rn + (long long)i * nu * I.ldu, I.ldu, 0, nu, nu, gs, L.ldq, kacc, lane);
             gemv_pairs<NRHS, G, RB>(a.Kb + I.Kb + (long long)i * nu * I.ldx, I.ldx, 0, nu, nx, gs, L.ldq, qacc, lane);
         } else {
