@@ -270,8 +270,10 @@ int dual_grad_noalloc(const tree_factors *f, const double *x0, const double *y, 
  *            instance order;
  *   knobs[2] cap on the wavefronts sharing one node above s*: 1, 2, 4, 8 or
  *            16 (default 16);
- *   knobs[3] stages above s*: 0 one launch per stage, a workgroup per node
- *            (default); 1 the backward stages in one launch in which each
+ *   knobs[3] stages above s*: 0 (default) one launch per stage, a workgroup
+ *            per node, or, on handles of few narrow trees (every nx + nu <= 32),
+ *            bands of stages, a workgroup walking one subtree of a band per
+ *            launch (with short chain parts too); 1 the backward stages in one launch in which each
  *            node is taken up by the workgroup that finishes its last child;
  *            2 one launch per stage, the nodes of instances with nx + nu <= 64
  *            walked by lane groups as the chains are; 3 (4) each instance's
@@ -447,7 +449,8 @@ int solve_info_batch(const tree_factors *f, solver_info *infos);
  * Phase timing for measurement tools.  stotree_timing(1) makes every sweep
  * record HIP events around each of its phases on the stream it runs on
  * (0 backward chain kernel, 1 backward per-stage kernels, 2 forward per-stage
- * kernels, 3 forward chain kernel); stotree_timing(0) stops recording.
+ * kernels, 3 forward chain kernel; in bands of stages the first band's
+ * forward pass counts in phase 1); stotree_timing(0) stops recording.
  * stotree_timing_read synchronises on the recorded events and writes, per
  * phase, the summed milliseconds (HOST ms[4]) and the number of launches
  * (HOST count[4]), then clears the record.  Process-wide state; not for use

@@ -676,6 +676,7 @@ void free_tree(tree_factors *f)
     for (auto &lv : f->rest_levels) free_level(lv);
     free_level(f->fused_bwd);
     free_level(f->fused_fwd);
+    free_bands(f);
     for (void *p : {(void *)f->panel_chain_items, (void *)f->trunk_entry.items, (void *)f->trunk_cnt,
                     (void *)f->Pcal})
         if (p) (void)hipFree(p);
@@ -689,6 +690,21 @@ int chain_group(int ldM, int group_min)
     return G < group_min ? group_min : G;
 }
 
+// Handles swept in bands of stages (bands.hip): every instance narrow (the
+// widths a band takes) and at most kBandChains chains in all.  The bands save
+// launches and latency, not bandwidth: per sweep against one launch per stage
+// (MI355X) 16 us against 46 on the 8-scenario tree with nx=4, nu=2; 62 against
+// 134 on the 4,095-node two-mode tree with nx=10, nu=4; 76 against 91 on 2,000
+// scenarios of 6 stages with nx=20, nu=10; level at 1,000 to 2,000 scenarios of
+// 15 stages of those blocks.  Wider blocks lose (nx=40, nu=20: 180 us against
+// 140: a lane group's rows are then one long serial product), and so does a
+// handle where wide instances need the per-stage launches anyway.  Chains of
+// more than kBandChainStages stages below s* stay with the chain kernel, whose
+// steps cost less there (129 us against 152 for a sweep of 243 chains of 10
+// stages with nx=20); shorter ones save its two launches.
+constexpr long long kBandChains = 8192;
+constexpr int kBandChainStages = 3;
+
 // Work lists of a sweep: the chains, one plan per lane-group width (each item
 // a wavefront's worth of consecutive chains of one instance; the costliest
 // first when chain_order is set) and, per stage above s*, all (instance,
@@ -701,13 +717,30 @@ int build_schedule(tree_factors *f)
     for (auto &lv : f->levels) free_level(lv);
     f->levels.clear();
     int max_sstar = 0, max_ldM = 0;
+    // launch form 0: the stages above s* in bands, and a short chain part with them
+    std::vector<std::vector<int>> cuts(f->ninst);
+    auto band_last = [](const InstDesc &I) { return I.N - I.sstar <= kBandChainStages ? I.N : I.sstar; };
+    if (f->trunk_fused == 0) {
+        long long nchains = 0;
+        for (const InstDesc &I : f->inst) nchains += I.nchains;
+        bool all = nchains <= kBandChains;
+        for (int b = 0; b < f->ninst && all; ++b) {
+            const InstDesc &I = f->inst[b];
+            if (b > 0 && f->shared > 1) cuts[b] = cuts[0];
+            else cuts[b] = band_cuts(I, f->sp_pool.data() + I.sp, f->cp_pool.data() + I.cp, band_last(I));
+            all = !cuts[b].empty();
+        }
+        if (!all) cuts.assign(f->ninst, {});
+    }
+    int rc = build_bands(f, cuts);
+    if (rc) return rc;
     std::map<int, std::vector<std::pair<double, Item>>> by_G;
     std::map<int, int> ldq_G;
     for (int b = 0; b < f->ninst; ++b) {
         const InstDesc &I = f->inst[b];
         max_sstar = std::max(max_sstar, I.sstar);
         max_ldM = std::max(max_ldM, I.ldM);
-        if (I.sstar >= I.N) continue;
+        if (I.sstar >= I.N || (!cuts[b].empty() && band_last(I) == I.N)) continue;
         const int G = chain_group(I.ldM, f->group_min);
         const int per = kWave / G;
         ldq_G[G] = std::max(ldq_G[G], I.ldM);
@@ -764,8 +797,9 @@ int build_schedule(tree_factors *f)
         STOTREE_HIP(hipMalloc(&lv.items, sizeof(Item) * std::max<size_t>(1, items.size())));
         f->levels.push_back(lv);
         STOTREE_HIP(hipMemcpy(lv.items, items.data(), sizeof(Item) * items.size(), hipMemcpyHostToDevice));
-        if (f->trunk_fused == 2) {
-            // lane groups for the nodes of narrow instances, workgroups for the rest
+        if (f->trunk_fused <= 2) {
+            // the nodes of the instances that are not swept in bands; in mode 2
+            // lane groups for the narrow ones, workgroups for the rest
             LevelPlan &L = f->levels.back();
             std::vector<Item> wide;
             std::map<int, std::vector<Item>> groups;
@@ -773,10 +807,10 @@ int build_schedule(tree_factors *f)
             int wide_ldM = 2;
             for (int b = 0; b < f->ninst; ++b) {
                 const InstDesc &I = f->inst[b];
-                if (t >= I.sstar) continue;
+                if (t >= I.sstar || !cuts[b].empty()) continue;
                 const int *sp = f->sp_pool.data() + I.sp;
                 const int G = chain_group(I.ldM, f->group_min);
-                if (G == kWave) {
+                if (f->trunk_fused != 2 || G == kWave) {
                     for (int i = sp[t]; i < sp[t + 1]; ++i) wide.push_back({b, i});
                     wide_ldM = std::max(wide_ldM, I.ldM);
                     continue;
@@ -1067,7 +1101,8 @@ int factor_forest(int count, const tree_desc *trees, const problem_data *datas, 
     f->m_tot = oy; f->x_tot = ox; f->u_tot = ou; f->nx_tot = ox0; f->mxu_tot = oxu;
     // host pools of the stage/child pointers
     f->sp_pool.resize(osp);
-    std::vector<int> cp_pool(ocp);
+    std::vector<int> &cp_pool = f->cp_pool;
+    cp_pool.resize(ocp);
     for (int b = 0; b < count; ++b) {
         const InstDesc &I = f->inst[b];
         std::memcpy(f->sp_pool.data() + I.sp, trees[b].stage_ptr, sizeof(int) * (I.N + 2));

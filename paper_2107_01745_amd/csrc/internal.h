@@ -80,10 +80,10 @@ struct ChainPlan {
     Item *items;                     // device: (instance, first chain)
 };
 
-// One launch of the per-stage kernels: all (instance, node) pairs of one stage.
-// With lane groups above s* (trunk mode 2) the stage is split into the nodes
-// of instances with nx + nu > 64 (workgroups of wide_nw wavefronts per node)
-// and lane-group items of kWave/G consecutive nodes of one instance.
+// One launch of the per-stage kernels: all (instance, node) pairs of one
+// stage, and how the nodes of the instances that are not swept in bands run:
+// workgroups of wide_nw wavefronts per node, or (trunk mode 2) lane-group items
+// of kWave/G consecutive nodes of one instance with nx + nu <= 64.
 struct LevelPlan {
     int t;
     int count;
@@ -92,6 +92,16 @@ struct LevelPlan {
     int wide_count = 0, wide_nw = 1;
     Item *wide_items = nullptr;
     std::vector<ChainPlan> narrow;
+};
+
+// One band of stages (bands.hip): the subtrees of every instance swept in
+// bands, by lane-group width (8, 16).
+struct BandPlan {
+    int count[2] = {0, 0};
+    int half[2] = {0, 0};         // doubles of the widest stage's node vectors of one right-hand side
+    int ldM[2] = {0, 0};          // largest padded nx + nu
+    int nw = 1;                      // wavefronts per subtree
+    Item *items[2] = {nullptr, nullptr};   // device: (instance, offset of the subtree's table)
 };
 
 // Solver workspace kept in the handle (allocated at the first solve).
@@ -119,7 +129,7 @@ struct tree_factors {
     int ninst = 0, precondition = 0;
     std::vector<stotree::InstDesc> inst;    // host copy
     stotree::InstDesc *d_inst = nullptr;
-    std::vector<int> sp_pool;               // host copy of the stage pointers
+    std::vector<int> sp_pool, cp_pool;      // host copies of the stage and child pointers
     int *d_sp = nullptr, *d_cp = nullptr, *d_anc = nullptr;  // anc: node-indexed (sc offsets)
     double *Mb = nullptr, *Mf = nullptr, *Kb = nullptr, *Kf = nullptr, *Rn = nullptr;
     double *chat = nullptr, *sig = nullptr, *cvec = nullptr, *sc = nullptr;
@@ -139,6 +149,8 @@ struct tree_factors {
     // schedule of a sweep
     std::vector<stotree::ChainPlan> chains;  // stages s*..N, one plan per lane-group width
     std::vector<stotree::LevelPlan> levels;  // stages 0..max(s*)-1
+    std::vector<stotree::BandPlan> bands;   // narrow instances' stages, first band at the root
+    int *band_tabs = nullptr;               // device: the subtrees' tables
     stotree::Item *panel_chain_items = nullptr;  // (instance, chain) pairs of the panel sweeps
     int npanel_chain_items = 0;
     // shared > 1: the instances are copies of instance 0 (same tree, factors
@@ -210,6 +222,13 @@ int enqueue_dual_grad(tree_factors *f, const double *x0, const double *y, int ho
 // scratch (no allocation).
 int dual_grad_noalloc_impl(const tree_factors *f, const double *x0, const double *y, int homogeneous, int nrhs,
                            double *x, double *u, hipStream_t st);
+
+// bands.hip
+std::vector<int> band_cuts(const InstDesc &I, const int *sp, const int *cp, int last);
+int build_bands(tree_factors *f, const std::vector<std::vector<int>> &cuts);
+void free_bands(tree_factors *f);
+// pass 0: backward, 1: forward, 2: both (band 0)
+void launch_band(const tree_factors *f, const SweepArgs &a, int nrhs, int band, int pass, hipStream_t st);
 
 // schedule.hip
 constexpr int kKnobs = 5;            // group_min, chain_order, trunk_cap, trunk_fused, panel_min

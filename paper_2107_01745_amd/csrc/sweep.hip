@@ -1624,16 +1624,13 @@ static void launch_trunk_fused(bool backward, const SweepArgs &a, const tree_fac
     }
 }
 
-// One stage above s*: per-node workgroups for every node, or (trunk mode 2)
-// lane groups for the narrow instances' nodes plus workgroups for the rest.
+// One stage above s* of the instances that are not swept in bands: per-node
+// workgroups for every node, or (trunk mode 2) lane groups for the narrow
+// instances' nodes plus workgroups for the rest.
 template <int NRHS, int CH>
 static void launch_level(bool backward, const SweepArgs &a, const tree_factors *f, const LevelPlan &lv, int ldM,
                          int qs, int ldu, hipStream_t st)
 {
-    if (f->trunk_fused != 2) {
-        launch_trunk<NRHS, CH>(backward, a, lv, ldM, qs, ldu, st);
-        return;
-    }
     if (lv.wide_count > 0) {
         LevelPlan w{};
         w.t = lv.t;
@@ -1721,7 +1718,7 @@ static hipError_t sweep_impl(const tree_factors *f, SweepArgs a, hipStream_t st)
         PhaseTimer tm(0, st);
         launch_chains<NRHS>(true, a, f, st);
     }
-    if (!f->levels.empty()) {
+    if (!f->levels.empty() || !f->bands.empty()) {
         PhaseTimer tm(1, st);
         if (f->trunk_fused == 1 && f->trunk_entry.count > 0) {
             launch_trunk_tree<NRHS, CH>(a, f, ldM, qs, ldu, st);
@@ -1733,9 +1730,10 @@ static hipError_t sweep_impl(const tree_factors *f, SweepArgs a, hipStream_t st)
         } else {
             for (int k = (int)f->levels.size() - 1; k >= 0; --k)
                 launch_level<NRHS, CH>(true, a, f, f->levels[k], ldM, qs, ldu, st);
+            for (int b = (int)f->bands.size() - 1; b >= 0; --b) launch_band(f, a, NRHS, b, b == 0 ? 2 : 0, st);
         }
     }
-    if (!f->levels.empty()) {
+    if (!f->levels.empty() || !f->bands.empty()) {
         PhaseTimer tm(2, st);
         if (f->trunk_fused >= 3) {
             if (f->fused_fwd.count > 0) launch_trunk_fused<NRHS, CH>(false, a, f, ldM, qs, st);
@@ -1744,6 +1742,7 @@ static hipError_t sweep_impl(const tree_factors *f, SweepArgs a, hipStream_t st)
         } else {
             for (size_t k = 0; k < f->levels.size(); ++k)
                 launch_level<NRHS, CH>(false, a, f, f->levels[k], ldM, qs, ldu, st);
+            for (size_t b = 1; b < f->bands.size(); ++b) launch_band(f, a, NRHS, (int)b, 1, st);
         }
     }
     if (!f->chains.empty()) {
