@@ -21,94 +21,162 @@ namespace stotree {
 
 namespace {
 
-constexpr int kTile = 64;    // output tile (rows and columns)
-constexpr int kKt = 16;      // reduction tile
-constexpr int kGB = 256;     // threads per GEMM block (16 x 16, 4 x 4 outputs each)
+typedef float v16f __attribute__((ext_vector_type(16)));
 
-// C[m][n] (+)= sum_k opA(m,k) opB(k,n) over k in [k0, k1), with
-// opA(m,k) = TA ? A[k*lda+m] : A[m*lda+k], opB(k,n) = TB ? B[n*ldb+k] : B[k*ldb+n].
+constexpr int kKt = 16;      // reduction rows staged in LDS at a time
+constexpr int kGB = 256;     // threads per GEMM block: four wavefronts
+constexpr int kLossThreads = 1024;   // threads per block of the loss passes
+
+// C[m][n] = sum_k opA(m,k) opB(k,n) over k in [k0, k1), with
+// opA(m,k) = TA ? A[k*lda+m] : A[m*lda+k], opB(k,n) = TB ? B[n*ldb+k] : B[k*ldb+n],
+// on the FP32 matrix cores (v_mfma_f32_32x32x2f32: FP32 products, FP32 sums).
 // Epilogue: + bias[n]; ReLU; or multiplication by the gate (G[m][n] > 0).
-// blockIdx.z selects a slice of the reduction (partial sums for the weight
-// gradients): A and B advance by z*kslice rows of the reduction, C by z*M*N.
-template <bool TA, bool TB>
+// With kslice > 0, blockIdx.z selects a slice of kslice rows of the reduction
+// (partial sums for the weight gradients, C advances by z*M*ldc) and csum, if
+// given, receives the slice's column sums of B (the bias gradients).
+//
+// Mapping: a block of BM x BN outputs, WR x WC wavefronts, each (BM/WR) x
+// (BN/WC) of them in 32 x 32 accumulators; the operands go through LDS in rows
+// of the reduction (an odd stride, so neither the transposing stores nor the
+// reads conflict) with the next rows' loads in flight during the products.
+// Bounds: the forward products move 40-65 MB of activations each at a
+// 65,536-row minibatch of the 128-unit network and run 11-14 us of matrix
+// work; the vector-unit tiles that stood here ran at 11 TFLOP/s (forward 42 us
+// a layer, weight gradients 98 us).
+// Operands (lane l): A[l%32][l/32], B[l/32][l%32], D[8(e/4) + 4(l/32) + e%4][l%32], e < 16.
+template <bool TA, bool TB, int BM, int BN, int WR, int WC>
 __global__ void __launch_bounds__(kGB) gemm_kernel(int M, int N, int K, const float *__restrict__ A, int lda,
                                                  const float *__restrict__ B, int ldb, float *__restrict__ C,
                                                  int ldc, const float *__restrict__ bias, int relu,
-                                                 const float *__restrict__ gate, int ldg, int kslice)
+                                                 const float *__restrict__ gate, int ldg, int kslice,
+                                                 float *__restrict__ csum)
 {
-    __shared__ float As[kKt][kTile + 4];
-    __shared__ float Bs[kKt][kTile + 4];
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    const int m0 = blockIdx.y * kTile, n0 = blockIdx.x * kTile;
+    static_assert(WR * WC * 64 == kGB, "four wavefronts");
+    constexpr int TM = BM / WR / 32, TN = BN / WC / 32;
+    constexpr int LA = BM * kKt / kGB, LB = BN * kKt / kGB;     // staged entries per thread
+    __shared__ float As[kKt][BM + 1];
+    __shared__ float Bs[kKt][BN + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+    const int wm = wave / WC * (BM / WR), wn = wave % WC * (BN / WC);
     int kbeg = 0, kend = K;
     if (kslice > 0) {
         kbeg = blockIdx.z * kslice;
         kend = min(K, kbeg + kslice);
         C += (long long)blockIdx.z * M * ldc;
     }
-    float acc[4][4] = {};
-    for (int k0 = kbeg; k0 < kend; k0 += kKt) {
-        // loads ordered so that consecutive threads read consecutive addresses
-        for (int e = threadIdx.x; e < kKt * kTile; e += kGB) {
-            const int kk = TA ? e / kTile : e % kKt, mm = TA ? e % kTile : e / kKt;
-            const int m = m0 + mm, k = k0 + kk;
-            As[kk][mm] = (m < M && k < kend) ? (TA ? A[(long long)k * lda + m] : A[(long long)m * lda + k]) : 0.0f;
+    // entry e of a tile: consecutive threads on consecutive addresses; entries
+    // past the matrix read a valid one and become zero on their way to LDS, so
+    // no load sits under a branch
+    float ra[LA], rb[LB];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int q = 0; q < LA; ++q) {
+            const int e = tid + kGB * q, kk = TA ? e / BM : e % kKt, mm = TA ? e % BM : e / kKt;
+            const int m = min(m0 + mm, M - 1), k = min(k0 + kk, kend - 1);
+            ra[q] = TA ? A[(long long)k * lda + m] : A[(long long)m * lda + k];
         }
-        for (int e = threadIdx.x; e < kKt * kTile; e += kGB) {
-            const int kk = TB ? e % kKt : e / kTile, nn = TB ? e / kKt : e % kTile;
-            const int n = n0 + nn, k = k0 + kk;
-            Bs[kk][nn] = (n < N && k < kend) ? (TB ? B[(long long)n * ldb + k] : B[(long long)k * ldb + n]) : 0.0f;
+#pragma unroll
+        for (int q = 0; q < LB; ++q) {
+            const int e = tid + kGB * q, kk = TB ? e % kKt : e / BN, nn = TB ? e / kKt : e % BN;
+            const int n = min(n0 + nn, N - 1), k = min(k0 + kk, kend - 1);
+            rb[q] = TB ? B[(long long)n * ldb + k] : B[(long long)k * ldb + n];
+        }
+    };
+    v16f acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+    const bool sums = csum && blockIdx.y == 0 && tid < BN;
+    float bsum = 0.0f;
+    fetch(kbeg);
+    for (int k0 = kbeg; k0 < kend; k0 += kKt) {
+#pragma unroll
+        for (int q = 0; q < LA; ++q) {
+            const int e = tid + kGB * q, kk = TA ? e / BM : e % kKt, mm = TA ? e % BM : e / kKt;
+            As[kk][mm] = m0 + mm < M && k0 + kk < kend ? ra[q] : 0.0f;
+        }
+#pragma unroll
+        for (int q = 0; q < LB; ++q) {
+            const int e = tid + kGB * q, kk = TB ? e % kKt : e / BN, nn = TB ? e / kKt : e % BN;
+            Bs[kk][nn] = n0 + nn < N && k0 + kk < kend ? rb[q] : 0.0f;
         }
         __syncthreads();
+        if (k0 + kKt < kend) fetch(k0 + kKt);
 #pragma unroll
-        for (int kk = 0; kk < kKt; ++kk) {
-            float a[4], b[4];
+        for (int kk = 0; kk < kKt; kk += 2) {
+            const int k = kk + lane / 32, c = lane & 31;
+            float a[TM], b[TN];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
+            for (int i = 0; i < TM; ++i) a[i] = As[k][wm + 32 * i + c];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx + 16 * j];
+            for (int j = 0; j < TN; ++j) b[j] = Bs[k][wn + 32 * j + c];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
         }
+        if (sums)
+#pragma unroll
+            for (int kk = 0; kk < kKt; ++kk) bsum += Bs[kk][tid];
         __syncthreads();
     }
+    if (sums && n0 + tid < N) csum[(long long)blockIdx.z * N + n0 + tid] = bsum;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty + 16 * i;
-        if (m >= M) continue;
+    for (int j = 0; j < TN; ++j) {
+        const int n = n0 + wn + 32 * j + (lane & 31);
+        if (n >= N) continue;
+        const float bn = bias ? bias[n] : 0.0f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx + 16 * j;
-            if (n >= N) continue;
-            float v = acc[i][j];
-            if (bias) v += bias[n];
-            if (relu) v = fmaxf(v, 0.0f);
-            if (gate && !(gate[(long long)m * ldg + n] > 0.0f)) v = 0.0f;
-            C[(long long)m * ldc + n] = v;
-        }
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int m = m0 + wm + 32 * i + 8 * (e / 4) + 4 * (lane / 32) + e % 4;
+                if (m >= M) continue;
+                float v = acc[i][j][e];
+                if (bias) v += bn;
+                if (relu) v = fmaxf(v, 0.0f);
+                if (gate && !(gate[(long long)m * ldg + n] > 0.0f)) v = 0.0f;
+                C[(long long)m * ldc + n] = v;
+            }
     }
 }
 
-// out[j] = sum_s part[s*n + j] (fixed order); also used for bias gradients
-// with part = dH (rows x n).
-__global__ void sum_rows_kernel(const float *part, int S, int n, float *out)
+// out[j] = sum_s part[s*n + j] in double, in a fixed order: 16 threads per
+// output take every 16th slice, then their sums are added pairwise.  A second
+// pair of arrays (the bias gradient's) rides along: outputs n .. n + n2.
+// (One thread per output walked its 128 slices one load at a time: 30 us.)
+__global__ void __launch_bounds__(256) sum_rows_kernel(const float *part, int S, int n, float *out,
+                                                       const float *part2, int n2, float *out2)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
+    const int j = blockIdx.x * 16 + (threadIdx.x & 15), g = threadIdx.x >> 4;
+    const bool second = j >= n;
+    const int jj = second ? j - n : j, nn = second ? n2 : n;
+    const float *p = second ? part2 : part;
     double s = 0.0;
-    for (int k = 0; k < S; ++k) s += part[(long long)k * n + j];
-    out[j] = (float)s;
+    if (j < n + n2)
+        for (int k = g; k < S; k += 16) s += p[(long long)k * nn + jj];
+    __shared__ double red[16][17];
+    red[g][threadIdx.x & 15] = s;
+    __syncthreads();
+    for (int h = 8; h > 0; h >>= 1) {
+        if (g < h) red[g][threadIdx.x & 15] += red[g + h][threadIdx.x & 15];
+        __syncthreads();
+    }
+    if (g == 0 && j < n + n2) (second ? out2 : out)[jj] = (float)red[0][threadIdx.x];
 }
 
 // Loss 1/count sum mask (Y - T)^2 and its gradient dY = 2 mask (Y - T)/count.
 // Per-block partial sums of the loss and of the mask go to part[2*block].
-// Device-side count of the mask: per-block sums (fixed order) into part,
-// then one thread forms 1 / max(1, sum).
-__global__ void mask_count_kernel(long long n, const float *mask, double *part)
+// Device-side count of the mask: per-block sums (fixed order) into part; every
+// block of the gradient pass adds them up.
+__global__ void __launch_bounds__(kLossThreads) mask_count_kernel(long long n, const float *mask, double *part)
 {
-    __shared__ double red[256];
+    __shared__ double red[kLossThreads];
     double c = 0.0;
     for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < n;
          k += (long long)gridDim.x * blockDim.x)
@@ -122,21 +190,34 @@ __global__ void mask_count_kernel(long long n, const float *mask, double *part)
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ void mask_inverse_kernel(const double *part, int nb, float *inv_out)
+// Sum of part[stride*k], k < nb <= 256, by a block of at least 256 threads (fixed
+// order), in every thread.
+__device__ __forceinline__ double block_sum(const double *part, int nb, int stride, double *red)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double c = 0.0;
-    for (int b = 0; b < nb; ++b) c += part[b];
-    inv_out[0] = (float)(1.0 / (c > 1.0 ? c : 1.0));
+    if (threadIdx.x < 256) red[threadIdx.x] = (int)threadIdx.x < nb ? part[stride * threadIdx.x] : 0.0;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        __syncthreads();
+    }
+    const double v = red[0];
+    __syncthreads();
+    return v;
 }
 
-// inv_dev: the inverse count from mask_count_kernel, or null (inv_count given)
-__global__ void mse_grad_kernel(long long n, const float *Y, const float *T, const float *mask, float inv_count,
-                                const float *inv_dev, float *dY, double *part)
+// counts: per-block counts of mask_count_kernel (each block adds them up and
+// takes 1 / max(1, sum)), or null (inv_count given)
+__global__ void __launch_bounds__(kLossThreads) mse_grad_kernel(long long n, const float *Y, const float *T, const float *mask,
+                                                       float inv_count, const double *counts, int ncounts, float *dY,
+                                                       double *part)
 {
-    __shared__ double red[2][256];
+    __shared__ double red[2][kLossThreads];
     double l = 0.0, c = 0.0;
-    const float inv = inv_dev ? inv_dev[0] : inv_count;
+    float inv = inv_count;
+    if (counts) {
+        const double t = block_sum(counts, ncounts, 1, red[0]);
+        inv = (float)(1.0 / (t > 1.0 ? t : 1.0));
+    }
     for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < n;
          k += (long long)gridDim.x * blockDim.x) {
         const float d = Y[k] - T[k];
@@ -161,13 +242,14 @@ __global__ void mse_grad_kernel(long long n, const float *Y, const float *T, con
     }
 }
 
-__global__ void sum_pairs_kernel(const double *part, int nb, double *out)
+__global__ void __launch_bounds__(256) sum_pairs_kernel(const double *part, int nb, double *out)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double l = 0.0, c = 0.0;
-    for (int b = 0; b < nb; ++b) { l += part[2 * b]; c += part[2 * b + 1]; }
-    out[0] = l;
-    out[1] = c;
+    __shared__ double red[256];
+    const double l = block_sum(part, nb, 2, red), c = block_sum(part + 1, nb, 2, red);
+    if (threadIdx.x == 0) {
+        out[0] = l;
+        out[1] = c;
+    }
 }
 
 // Adam (Kingma and Ba 2015) with bias correction.
@@ -193,59 +275,67 @@ struct WarmArgs {
     float c_scale;
 };
 
-// One thread per (node, feature).
-__global__ void features_kernel(WarmArgs a, int b, float *X, long long row0)
+// The node passes run every instance in one launch (blockIdx.y; ninst of
+// them), its rows starting at its first node; per instance a launch took 3-8 us
+// for 1-3 us of work.  Ix: type of an element index inside an instance, 32 bits
+// where they suffice (the divisions are several times cheaper).
+
+// One thread per (node, state entry): its x0, c and path-mean features and
+// every nx-th entry of the one-hot stage.  (The walk to the root is a chain of
+// dependent loads; a thread per feature put it into almost every wavefront
+// for a quarter of its lanes.)
+template <typename Ix>
+__global__ void features_kernel(WarmArgs a, int ninst, float *X)
 {
-    const InstDesc I = a.inst[b];
-    const int *sp = a.sp + I.sp;
-    const int *anc = a.anc + I.sc;  // node-indexed pools share the sc offset
-    const long long total = (long long)I.V * a.din;
-    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
-         e += (long long)gridDim.x * blockDim.x) {
-        const int i = (int)(e / a.din), f = (int)(e % a.din);
-        int t = 0;
-        while (t < I.N && sp[t + 1] <= i) ++t;
-        float v = 0.0f;
-        if (f < I.nx) {
-            v = (float)a.x0[I.x0 + f];
-        } else if (f < 2 * I.nx) {
-            v = (float)(a.cvec[I.c + (long long)i * I.nx + (f - I.nx)] / a.c_scale);
-        } else if (f < 3 * I.nx) {
-            const int col = f - 2 * I.nx;
+    for (int b = blockIdx.y; b < ninst; b += gridDim.y) {
+        const InstDesc I = a.inst[b];
+        const int *sp = a.sp + I.sp;
+        const int *anc = a.anc + I.sc;  // node-indexed pools share the sc offset
+        const double *cv = a.cvec + I.c;
+        const Ix total = (Ix)I.V * I.nx;
+        float *Xb = X + I.node0 * a.din;
+        for (Ix e = (Ix)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (Ix)gridDim.x * blockDim.x) {
+            const int i = (int)(e / I.nx), col = (int)(e - (Ix)i * I.nx);
+            float *x = Xb + (long long)i * a.din;
             double s = 0.0;
-            for (int j = i; j > 0; j = anc[j]) s += a.cvec[I.c + (long long)j * I.nx + col];
-            v = t > 0 ? (float)(s / t / a.c_scale) : 0.0f;
-        } else {
-            v = (f - 3 * I.nx == t) ? 1.0f : 0.0f;
+            int t = 0;                   // the stage: edges on the path to the root
+            for (int j = i; j > 0; j = anc[j], ++t) s += cv[(long long)j * I.nx + col];
+            x[col] = (float)a.x0[I.x0 + col];
+            x[I.nx + col] = (float)(cv[e] / a.c_scale);
+            x[2 * I.nx + col] = t > 0 ? (float)(s / t / a.c_scale) : 0.0f;
+            for (int f = col; f <= I.N; f += I.nx) x[3 * I.nx + f] = f == t ? 1.0f : 0.0f;
         }
-        X[(row0 + i) * a.din + f] = v;
     }
 }
 
 // Y rows (scaled by y_scale) -> dual vector (root state rows 0), and the
 // inverse map dual -> target rows with a mask of the rows that exist.
-__global__ void scatter_kernel(WarmArgs a, int b, const float *Y, long long row0, double *y, float y_scale)
+template <typename Ix>
+__global__ void scatter_kernel(WarmArgs a, int ninst, const float *Y, double *y, float y_scale)
 {
+    for (int b = blockIdx.y; b < ninst; b += gridDim.y) {
     const InstDesc I = a.inst[b];
-    for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < I.m;
-         k += (long long)gridDim.x * blockDim.x) {
-        const long long nl = (long long)I.Vnl * (I.nx + I.nu);
-        int i, col;
-        if (k < nl) { i = (int)(k / (I.nx + I.nu)); col = (int)(k % (I.nx + I.nu)); }
-        else { i = I.Vnl + (int)((k - nl) / I.nx); col = (int)((k - nl) % I.nx); }
-        const double v = (i == 0 && col < I.nx) ? 0.0 : (double)Y[(row0 + i) * a.dout + col] * y_scale;
+    const Ix W = I.nx + I.nu, nl = (Ix)I.Vnl * W, m = (Ix)I.m;
+    const float *Yb = Y + I.node0 * a.dout;
+    for (Ix k = (Ix)blockIdx.x * blockDim.x + threadIdx.x; k < m; k += (Ix)gridDim.x * blockDim.x) {
+        Ix i, col;
+        if (k < nl) { i = k / W; col = k - i * W; }
+        else { i = (k - nl) / I.nx; col = k - nl - i * I.nx; i += I.Vnl; }
+        const double v = (i == 0 && (int)col < I.nx) ? 0.0 : (double)Yb[(long long)i * a.dout + col] * y_scale;
         y[I.y + k] = v;
+    }
     }
 }
 
-__global__ void targets_kernel(WarmArgs a, int b, const double *y, long long row0, float *T, float *mask,
-                               float inv_scale)
+template <typename Ix>
+__global__ void targets_kernel(WarmArgs a, int ninst, const double *y, float *T, float *mask, float inv_scale)
 {
+    for (int b = blockIdx.y; b < ninst; b += gridDim.y) {
     const InstDesc I = a.inst[b];
-    const long long total = (long long)I.V * a.dout;
-    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
-         e += (long long)gridDim.x * blockDim.x) {
-        const int i = (int)(e / a.dout), col = (int)(e % a.dout);
+    const Ix total = (Ix)I.V * a.dout;
+    float *Tb = T + I.node0 * a.dout, *Mb = mask + I.node0 * a.dout;
+    for (Ix e = (Ix)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (Ix)gridDim.x * blockDim.x) {
+        const int i = (int)(e / a.dout), col = (int)(e - (Ix)i * a.dout);
         const int w = i < I.Vnl ? I.nx + I.nu : I.nx;
         float t = 0.0f, mk = 0.0f;
         if (col < w && !(i == 0 && col < I.nx)) {
@@ -253,27 +343,40 @@ __global__ void targets_kernel(WarmArgs a, int b, const double *y, long long row
             t = (float)(y[I.y + o + col] * inv_scale);
             mk = 1.0f;
         }
-        T[(row0 + i) * a.dout + col] = t;
-        mask[(row0 + i) * a.dout + col] = mk;
+        Tb[e] = t;
+        Mb[e] = mk;
+    }
     }
 }
 
-int launch_gemm(bool ta, bool tb, int M, int N, int K, const float *A, int lda, const float *B, int ldb, float *C,
-                int ldc, const float *bias, int relu, const float *gate, int ldg, int kslice, int nslices,
-                hipStream_t st)
+template <bool TA, bool TB, int BM, int BN, int WR, int WC>
+void launch_tile(int M, int N, int K, const float *A, int lda, const float *B, int ldb, float *C, int ldc,
+                 const float *bias, int relu, const float *gate, int ldg, int kslice, int nslices, float *csum,
+                 hipStream_t st)
 {
-    const dim3 grid((N + kTile - 1) / kTile, (M + kTile - 1) / kTile, nslices);
-    if (!ta && !tb)
-        hipLaunchKernelGGL((gemm_kernel<false, false>), grid, dim3(kGB), 0, st, M, N, K, A, lda, B, ldb, C, ldc,
-                           bias, relu, gate, ldg, kslice);
-    else if (!ta && tb)
-        hipLaunchKernelGGL((gemm_kernel<false, true>), grid, dim3(kGB), 0, st, M, N, K, A, lda, B, ldb, C, ldc,
-                           bias, relu, gate, ldg, kslice);
-    else if (ta && !tb)
-        hipLaunchKernelGGL((gemm_kernel<true, false>), grid, dim3(kGB), 0, st, M, N, K, A, lda, B, ldb, C, ldc,
-                           bias, relu, gate, ldg, kslice);
+    const dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM, nslices);
+    hipLaunchKernelGGL((gemm_kernel<TA, TB, BM, BN, WR, WC>), grid, dim3(kGB), 0, st, M, N, K, A, lda, B, ldb, C,
+                       ldc, bias, relu, gate, ldg, kslice, csum);
+}
+
+// Tiles of the row products (C has one row per node row): as wide as the
+// columns, so that the activations are read once; 128 rows tall where that
+// still gives every compute unit a block, 32 (64 for narrow outputs) below.
+template <bool TB>
+int launch_rows(int M, int N, int K, const float *A, int lda, const float *B, int ldb, float *C, int ldc,
+                const float *bias, int relu, const float *gate, int ldg, hipStream_t st)
+{
+    const bool tall = M >= 128 * 256;
+    if (N <= 32)
+        launch_tile<false, TB, 128, 32, 4, 1>(M, N, K, A, lda, B, ldb, C, ldc, bias, relu, gate, ldg, 0, 1, nullptr, st);
+    else if (N <= 64 && tall)
+        launch_tile<false, TB, 128, 64, 2, 2>(M, N, K, A, lda, B, ldb, C, ldc, bias, relu, gate, ldg, 0, 1, nullptr, st);
+    else if (N <= 64)
+        launch_tile<false, TB, 64, 64, 2, 2>(M, N, K, A, lda, B, ldb, C, ldc, bias, relu, gate, ldg, 0, 1, nullptr, st);
+    else if (tall)
+        launch_tile<false, TB, 128, 128, 2, 2>(M, N, K, A, lda, B, ldb, C, ldc, bias, relu, gate, ldg, 0, 1, nullptr, st);
     else
-        return STOTREE_ERR_ARG;
+        launch_tile<false, TB, 32, 128, 1, 4>(M, N, K, A, lda, B, ldb, C, ldc, bias, relu, gate, ldg, 0, 1, nullptr, st);
     STOTREE_HIP(hipGetLastError());
     return STOTREE_OK;
 }
@@ -336,11 +439,11 @@ int mlp_forward_impl(int rows, int din, int dh, int dout, const float *P, const 
     const Layout L = layout(din, dh, dout);
     float *H1 = H, *H2 = H + (long long)rows * dh;
     int rc;
-    if ((rc = launch_gemm(false, false, rows, dh, din, X, din, P + L.W1, dh, H1, dh, P + L.b1, 1, nullptr, 0, 0, 1, st)))
+    if ((rc = launch_rows<false>(rows, dh, din, X, din, P + L.W1, dh, H1, dh, P + L.b1, 1, nullptr, 0, st)))
         return rc;
-    if ((rc = launch_gemm(false, false, rows, dh, dh, H1, dh, P + L.W2, dh, H2, dh, P + L.b2, 1, nullptr, 0, 0, 1, st)))
+    if ((rc = launch_rows<false>(rows, dh, dh, H1, dh, P + L.W2, dh, H2, dh, P + L.b2, 1, nullptr, 0, st)))
         return rc;
-    return launch_gemm(false, false, rows, dout, dh, H2, dh, P + L.W3, dout, Y, dout, P + L.b3, 0, nullptr, 0, 0, 1, st);
+    return launch_rows<false>(rows, dout, dh, H2, dh, P + L.W3, dout, Y, dout, P + L.b3, 0, nullptr, 0, st);
 }
 
 long long mlp_work_len(int rows, int din, int dh, int dout)
@@ -352,13 +455,14 @@ long long mlp_work_len(int rows, int din, int dh, int dout)
 
 namespace {
 // dst[r][:] = src[idx[r]][:] for r < rows (cols floats per row)
+template <typename Ix>
 __global__ void gather_rows_kernel(long long rows, int cols, const float *src, long long src_rows,
                                    const long long *idx, float *dst, int *bad)
 {
-    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < rows * cols;
-         e += (long long)gridDim.x * blockDim.x) {
-        const long long r = e / cols;
-        const int c = (int)(e - r * cols);
+    const Ix total = (Ix)(rows * cols);
+    for (Ix e = (Ix)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (Ix)gridDim.x * blockDim.x) {
+        const Ix r = e / (Ix)cols;
+        const int c = (int)(e - r * (Ix)cols);
         const long long s = idx[r];
         if (s < 0 || s >= src_rows) {   // an index outside the source: flagged, entry left as is
             *bad = 1;
@@ -368,19 +472,18 @@ __global__ void gather_rows_kernel(long long rows, int cols, const float *src, l
     }
 }
 
-__global__ void fill_f32_kernel(float *v, long long n, float val)
-{
-    for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < n; k += (long long)gridDim.x * blockDim.x)
-        v[k] = val;
-}
-
-// out[n] = sum over rows of D (rows x n), as ones' D in fixed-order slices.
-int colsum(int rows, int n, const float *D, const float *ones, float *part, float *out, hipStream_t st)
+// Gradient of one layer: G[W] = A' D and G[b] = column sums of D over the rows,
+// in slices of kSliceRows rows (partial sums in part and partb), added up in a
+// fixed order.
+int layer_grad(int rows, int M, int N, const float *A, const float *D, float *part, float *partb, float *GW,
+               float *Gb, hipStream_t st)
 {
     const int slices = (rows + kSliceRows - 1) / kSliceRows;
-    int rc = launch_gemm(true, false, 1, n, rows, ones, 1, D, n, part, n, nullptr, 0, nullptr, 0, kSliceRows, slices, st);
-    if (rc) return rc;
-    hipLaunchKernelGGL(sum_rows_kernel, dim3((n + 255) / 256), dim3(256), 0, st, part, slices, n, out);
+    launch_tile<true, false, 64, 64, 2, 2>(M, N, rows, A, M, D, N, part, N, nullptr, 0, nullptr, 0, kSliceRows, slices,
+                                           partb, st);
+    hipLaunchKernelGGL(sum_rows_kernel, dim3((M * N + N + 15) / 16), dim3(256), 0, st, part, slices, M * N, GW, partb,
+                       N, Gb);
+    STOTREE_HIP(hipGetLastError());
     return STOTREE_OK;
 }
 }  // namespace
@@ -393,51 +496,31 @@ int mlp_backward_impl(int rows, int din, int dh, int dout, const float *P, const
     float *dH2 = work, *dH1 = work + (long long)rows * dh, *part = work + 2LL * rows * dh;
     const int slices = (rows + kSliceRows - 1) / kSliceRows;
     const long long wmax = std::max<long long>((long long)din * dh, std::max<long long>((long long)dh * dh, (long long)dh * dout));
-    float *ones = part + (long long)slices * wmax, *partb = ones + rows;
-    hipLaunchKernelGGL(fill_f32_kernel, dim3(256), dim3(256), 0, st, ones, (long long)rows, 1.0f);
+    float *partb = part + (long long)slices * wmax;
     int rc;
     // layer 3
-    if ((rc = launch_gemm(true, false, dh, dout, rows, H2, dh, dY, dout, part, dout, nullptr, 0, nullptr, 0,
-                          kSliceRows, slices, st)))
-        return rc;
-    hipLaunchKernelGGL(sum_rows_kernel, dim3((dh * dout + 255) / 256), dim3(256), 0, st, part, slices, dh * dout, G + L.W3);
-    if ((rc = colsum(rows, dout, dY, ones, partb, G + L.b3, st))) return rc;
-    if ((rc = launch_gemm(false, true, rows, dh, dout, dY, dout, P + L.W3, dout, dH2, dh, nullptr, 0, H2, dh, 0, 1, st)))
-        return rc;
+    if ((rc = layer_grad(rows, dh, dout, H2, dY, part, partb, G + L.W3, G + L.b3, st))) return rc;
+    if ((rc = launch_rows<true>(rows, dh, dout, dY, dout, P + L.W3, dout, dH2, dh, nullptr, 0, H2, dh, st))) return rc;
     // layer 2
-    if ((rc = launch_gemm(true, false, dh, dh, rows, H1, dh, dH2, dh, part, dh, nullptr, 0, nullptr, 0, kSliceRows,
-                          slices, st)))
-        return rc;
-    hipLaunchKernelGGL(sum_rows_kernel, dim3((dh * dh + 255) / 256), dim3(256), 0, st, part, slices, dh * dh, G + L.W2);
-    if ((rc = colsum(rows, dh, dH2, ones, partb, G + L.b2, st))) return rc;
-    if ((rc = launch_gemm(false, true, rows, dh, dh, dH2, dh, P + L.W2, dh, dH1, dh, nullptr, 0, H1, dh, 0, 1, st)))
-        return rc;
+    if ((rc = layer_grad(rows, dh, dh, H1, dH2, part, partb, G + L.W2, G + L.b2, st))) return rc;
+    if ((rc = launch_rows<true>(rows, dh, dh, dH2, dh, P + L.W2, dh, dH1, dh, nullptr, 0, H1, dh, st))) return rc;
     // layer 1
-    if ((rc = launch_gemm(true, false, din, dh, rows, X, din, dH1, dh, part, dh, nullptr, 0, nullptr, 0, kSliceRows,
-                          slices, st)))
-        return rc;
-    hipLaunchKernelGGL(sum_rows_kernel, dim3((din * dh + 255) / 256), dim3(256), 0, st, part, slices, din * dh, G + L.W1);
-    if ((rc = colsum(rows, dh, dH1, ones, partb, G + L.b1, st))) return rc;
-    STOTREE_HIP(hipGetLastError());
-    return STOTREE_OK;
+    return layer_grad(rows, din, dh, X, dH1, part, partb, G + L.W1, G + L.b1, st);
 }
 
 int mse_grad_impl(long long n, const float *Y, const float *T, const float *mask, float inv_count, float *dY,
                   double *loss2, double *part, hipStream_t st)
 {
-    // 255 blocks: their (loss, count) pairs fill the first 510 of the 512
-    // scratch doubles; with inv_count 0 the inverse count, 1 / max(1, sum
-    // mask), formed on the device, goes in the 511th
-    const int nb = 255;
-    float *inv_dev = nullptr;
+    // 170 blocks: the (loss, count) pairs fill 340 of the 512 scratch doubles;
+    // with inv_count 0 the per-block counts fill the 170 after them
+    const int nb = 170;
+    double *counts = nullptr;
     if (inv_count == 0.0f) {
-        // the per-block counts use the scratch before the loss pairs overwrite it
-        inv_dev = reinterpret_cast<float *>(part + 2 * nb);
-        hipLaunchKernelGGL(mask_count_kernel, dim3(nb), dim3(256), 0, st, n, mask, part);
-        hipLaunchKernelGGL(mask_inverse_kernel, dim3(1), dim3(64), 0, st, part, nb, inv_dev);
+        counts = part + 2 * nb;
+        hipLaunchKernelGGL(mask_count_kernel, dim3(nb), dim3(kLossThreads), 0, st, n, mask, counts);
     }
-    hipLaunchKernelGGL(mse_grad_kernel, dim3(nb), dim3(256), 0, st, n, Y, T, mask, inv_count, inv_dev, dY, part);
-    hipLaunchKernelGGL(sum_pairs_kernel, dim3(1), dim3(64), 0, st, part, nb, loss2);
+    hipLaunchKernelGGL(mse_grad_kernel, dim3(nb), dim3(kLossThreads), 0, st, n, Y, T, mask, inv_count, counts, nb, dY, part);
+    hipLaunchKernelGGL(sum_pairs_kernel, dim3(1), dim3(256), 0, st, part, nb, loss2);
     STOTREE_HIP(hipGetLastError());
     return STOTREE_OK;
 }
@@ -446,7 +529,11 @@ int gather_rows_impl(long long rows, int cols, const float *src, long long src_r
                      float *dst, int *bad, hipStream_t st)
 {
     const unsigned g = (unsigned)std::min<long long>(2048, (rows * cols + 255) / 256);
-    hipLaunchKernelGGL(gather_rows_kernel, dim3(g), dim3(256), 0, st, rows, cols, src, src_rows, idx, dst, bad);
+    if (rows * cols < 1LL << 31)
+        hipLaunchKernelGGL(gather_rows_kernel<unsigned>, dim3(g), dim3(256), 0, st, rows, cols, src, src_rows, idx, dst, bad);
+    else
+        hipLaunchKernelGGL(gather_rows_kernel<unsigned long long>, dim3(g), dim3(256), 0, st, rows, cols, src, src_rows, idx,
+                           dst, bad);
     STOTREE_HIP(hipGetLastError());
     return STOTREE_OK;
 }
@@ -460,18 +547,30 @@ int adam_impl(long long n, float *p, const float *g, float *m, float *v, float l
     return STOTREE_OK;
 }
 
+namespace {
+// Grid of a node pass: enough blocks of 256 for the largest instance's
+// elements (at most 1024), a row of them per instance.
+struct NodeGrid {
+    dim3 grid;
+    bool small;                      // 32-bit element indices
+};
+NodeGrid node_grid(const tree_factors *f, long long per_node)
+{
+    long long most = 1;
+    for (const InstDesc &I : f->inst) most = std::max(most, (long long)I.V * per_node);
+    return {dim3((unsigned)std::min<long long>(1024, (most + 255) / 256), (unsigned)std::min(f->ninst, 32768)),
+            most < 1LL << 31};
+}
+}  // namespace
+
 int warm_features_impl(const tree_factors *f, const double *x0, float c_scale, float *X, hipStream_t st)
 {
     int rc = uniform_instances(f, "warm_features");
     if (rc) return rc;
     const WarmArgs a = warm_args(f, x0, c_scale);
-    long long row = 0;
-    for (int b = 0; b < f->ninst; ++b) {
-        const InstDesc &I = f->inst[b];
-        const unsigned g = (unsigned)std::min<long long>(1024, ((long long)I.V * a.din + 255) / 256);
-        hipLaunchKernelGGL(features_kernel, dim3(g), dim3(256), 0, st, a, b, X, row);
-        row += I.V;
-    }
+    const NodeGrid g = node_grid(f, f->inst[0].nx);
+    if (g.small) hipLaunchKernelGGL(features_kernel<unsigned>, g.grid, dim3(256), 0, st, a, f->ninst, X);
+    else hipLaunchKernelGGL(features_kernel<unsigned long long>, g.grid, dim3(256), 0, st, a, f->ninst, X);
     STOTREE_HIP(hipGetLastError());
     return STOTREE_OK;
 }
@@ -481,13 +580,9 @@ int warm_scatter_impl(const tree_factors *f, const float *Y, float y_scale, doub
     int rc = uniform_instances(f, "warm_scatter");
     if (rc) return rc;
     const WarmArgs a = warm_args(f, nullptr, 1.0f);
-    long long row = 0;
-    for (int b = 0; b < f->ninst; ++b) {
-        const InstDesc &I = f->inst[b];
-        const unsigned g = (unsigned)std::min<long long>(1024, (I.m + 255) / 256);
-        hipLaunchKernelGGL(scatter_kernel, dim3(g), dim3(256), 0, st, a, b, Y, row, y, y_scale);
-        row += I.V;
-    }
+    const NodeGrid g = node_grid(f, a.dout);
+    if (g.small) hipLaunchKernelGGL(scatter_kernel<unsigned>, g.grid, dim3(256), 0, st, a, f->ninst, Y, y, y_scale);
+    else hipLaunchKernelGGL(scatter_kernel<unsigned long long>, g.grid, dim3(256), 0, st, a, f->ninst, Y, y, y_scale);
     STOTREE_HIP(hipGetLastError());
     return STOTREE_OK;
 }
@@ -497,13 +592,9 @@ int warm_targets_impl(const tree_factors *f, const double *y, float y_scale, flo
     int rc = uniform_instances(f, "warm_targets");
     if (rc) return rc;
     const WarmArgs a = warm_args(f, nullptr, 1.0f);
-    long long row = 0;
-    for (int b = 0; b < f->ninst; ++b) {
-        const InstDesc &I = f->inst[b];
-        const unsigned g = (unsigned)std::min<long long>(1024, ((long long)I.V * a.dout + 255) / 256);
-        hipLaunchKernelGGL(targets_kernel, dim3(g), dim3(256), 0, st, a, b, y, row, T, mask, 1.0f / y_scale);
-        row += I.V;
-    }
+    const NodeGrid g = node_grid(f, a.dout);
+    if (g.small) hipLaunchKernelGGL(targets_kernel<unsigned>, g.grid, dim3(256), 0, st, a, f->ninst, y, T, mask, 1.0f / y_scale);
+    else hipLaunchKernelGGL(targets_kernel<unsigned long long>, g.grid, dim3(256), 0, st, a, f->ninst, y, T, mask, 1.0f / y_scale);
     STOTREE_HIP(hipGetLastError());
     return STOTREE_OK;
 }
