@@ -49,6 +49,7 @@ constexpr int kMemMax = 16;   // L-BFGS memory supported on the device
 constexpr int kNuCap = 30;    // largest nu_max
 constexpr int kNuDefault = 10; // default nu_max
 constexpr int kVB = 256;      // threads per block of the vector kernels
+constexpr int kFin = 512;     // threads per block of the finalize kernels
 
 constexpr int kBtMax = 50;     // halvings of lambda before an instance gives up
 constexpr int kTraceCols = 40; // trace row: lambda, res, accepted nu, nu_max, pairs, dphi[nu]...
@@ -196,21 +197,60 @@ __device__ __forceinline__ double wave_red(double x, bool is_max)
     return x;
 }
 
-// Block-reduce acc[0..nv) and store slot v of this block at part[v*nblocks+b].
-template <int NV>
-__device__ void block_store(double (&acc)[NV], int nv, double *part, int nblocks)
+// Sums over the wavefront of v[0..N), value idx left in the lanes that return
+// idx (ok): at each exchange a lane keeps half of the values and hands the
+// other half to its partner, so N values take about N exchanges instead of
+// 6 N (the same pairs are added as by one butterfly per value).
+template <int N, int OFF, int M>
+__device__ __forceinline__ int fold_sums(double (&v)[M], int lane, bool &ok)
 {
+    constexpr int H = (N + 1) / 2;
+    const bool hi = (lane & OFF) != 0;
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+        const double a = v[j], b = j + H < N ? v[j + H] : 0.0;
+        v[j] = (hi ? b : a) + __shfl_xor(hi ? a : b, OFF, 64);
+    }
+    int idx = 0;
+    if constexpr (OFF > 1) idx = fold_sums<H, OFF / 2>(v, lane, ok);
+    idx += hi ? H : 0;
+    ok = ok && idx < N;
+    return idx;
+}
+
+// Block-reduce acc and store slot v < NV of this block at part[v*nblocks+b]:
+// slots [0, kNMax) are maxima (with MAXES; otherwise nothing reads them), the
+// rest sums.
+template <int NV, bool MAXES = true>
+__device__ void block_store(double (&acc)[NV], double *part, int nblocks)
+{
+    constexpr int NS = NV - kNMax;
+    static_assert(NS <= 128, "two folds");
     __shared__ double red[kVB / 64][NV];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (MAXES)
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        if (v < nv) {
-            const double x = wave_red(acc[v], v < kNMax);
+        for (int v = 0; v < kNMax; ++v) {
+            const double x = wave_red(acc[v], true);
             if (lane == 0) red[w][v] = x;
         }
+    constexpr int N0 = NS < 64 ? NS : 64;
+    double s0[N0];
+#pragma unroll
+    for (int v = 0; v < N0; ++v) s0[v] = acc[kNMax + v];
+    bool ok = true;
+    const int i0 = fold_sums<N0, 32>(s0, lane, ok);
+    if (ok) red[w][kNMax + i0] = s0[0];
+    if constexpr (NS > 64) {
+        double s1[NS - 64];
+#pragma unroll
+        for (int v = 64; v < NS; ++v) s1[v - 64] = acc[kNMax + v];
+        ok = true;
+        const int i1 = fold_sums<NS - 64, 32>(s1, lane, ok);
+        if (ok) red[w][kNMax + 64 + i1] = s1[0];
     }
     __syncthreads();
-    for (int v = threadIdx.x; v < nv; v += blockDim.x) {
+    for (int v = threadIdx.x + (MAXES ? 0 : kNMax); v < NV; v += blockDim.x) {
         double x = red[0][v];
         for (int k = 1; k < kVB / 64; ++k) x = (v < kNMax) ? fmax(x, red[k][v]) : x + red[k][v];
         part[(long long)v * nblocks + blockIdx.x] = x;
@@ -218,20 +258,39 @@ __device__ void block_store(double (&acc)[NV], int nv, double *part, int nblocks
 }
 
 // Finalize-side reduction of nv slots over blocks [first, first+count) (fixed
-// order) into out.
+// order) into out; a wavefront per slot.
 __device__ void reduce_partials(const double *part, int nblocks, int first, int count, int nv, double *out)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     for (int v = w; v < nv; v += nw) {
         const bool mx = v < kNMax;
+        const double *p = part + (long long)v * nblocks + first;
         double x = 0.0;
-        for (int b = first + lane; b < first + count; b += 64) {
-            const double p = part[(long long)v * nblocks + b];
-            x = mx ? fmax(x, p) : x + p;
+        // four loads in flight (blocks past the end re-read the first one and are not added)
+        for (int b = lane; b < count; b += 256) {
+            double q[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) q[u] = p[b + 64 * u < count ? b + 64 * u : b];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (b + 64 * u < count) x = mx ? fmax(x, q[u]) : x + q[u];
         }
         x = wave_red(x, mx);
         if (lane == 0) out[v] = x;
     }
+    __syncthreads();
+}
+
+// The finalize kernels take their decisions on a copy of the control block in
+// LDS (one thread's chain of dependent accesses: from memory and with its small
+// arrays in scratch it took 15 us on the smallest problems) and write it back
+// whole.
+__device__ __forceinline__ void ctl_copy(Ctl *dst, const Ctl *src)
+{
+    static_assert(sizeof(Ctl) % 8 == 0, "copied in doubles");
+    double *d = reinterpret_cast<double *>(dst);
+    const double *s = reinterpret_cast<const double *>(src);
+    for (int k = threadIdx.x; k < (int)(sizeof(Ctl) / 8); k += blockDim.x) d[k] = s[k];
     __syncthreads();
 }
 
@@ -276,9 +335,9 @@ __global__ void __launch_bounds__(kVB) resid_kernel(VecArgs a)
     const Ctl *c = a.ctl + br.b;
     if (idle(c)) return;
     constexpr int NV = PAIR ? nv_pair(MEMCAP) : PB;
-    double acc[nv_pair(MEMCAP)];
+    double acc[NV];
 #pragma unroll
-    for (int v = 0; v < nv_pair(MEMCAP); ++v) acc[v] = 0.0;
+    for (int v = 0; v < NV; ++v) acc[v] = 0.0;
     const double lam = c->lam;
     const bool have_pair = PAIR && c->have_pair;
     const int cnt = c->cnt, fslot = c->free_slot;
@@ -304,7 +363,7 @@ __global__ void __launch_bounds__(kVB) resid_kernel(VecArgs a)
             pair_dots<MEMCAP>(a, k, sv, qv, R, have_pair, cnt, fslot, order, acc);
         }
     }
-    block_store<nv_pair(MEMCAP)>(acc, NV, a.part, a.nblocks);
+    block_store(acc, a.part, a.nblocks);
 }
 
 // MINFBE gradient of the FBE and the L-BFGS pair/dots; slot R_SS collects
@@ -334,7 +393,7 @@ __global__ void __launch_bounds__(kVB) grad_kernel(VecArgs a)
         const double qv = have_pair ? g - a.gp[k] : 0.0;
         pair_dots<MEMCAP>(a, k, sv, qv, g, have_pair, cnt, fslot, order, acc);
     }
-    block_store<nv_pair(MEMCAP)>(acc, nv_pair(MEMCAP), a.part, a.nblocks);
+    block_store(acc, a.part, a.nblocks);
 }
 
 template <int MEMCAP>
@@ -359,12 +418,51 @@ __global__ void __launch_bounds__(kVB) combine_kernel(VecArgs a)
     }
 }
 
+// The row prox of a line search, where one row is tried at many points: the
+// quotients that do not depend on the point, formed once.
+struct RowTrial {
+    double lo, hi, w, d, wl, q, h;   // wl = w / lambda, q = 1 + wl / d, h = w / (2 d)
+};
+__device__ __forceinline__ RowTrial row_trial(const RowG &g, double lam)
+{
+    RowTrial t{g.lo, g.hi, g.w, g.d, 0.0, 1.0, 0.0};
+    if (g.w < INFINITY) {
+        t.wl = g.w / lam;
+        if (g.d > 0.0) {
+            t.q = 1.0 + t.wl / g.d;
+            t.h = g.w / (2.0 * g.d);
+        }
+    }
+    return t;
+}
+__device__ __forceinline__ double row_prox(double v, const RowTrial &g, double &gz)
+{
+    gz = 0.0;
+    const double in = v < g.lo ? g.lo : (v > g.hi ? g.hi : v);
+    if (!(g.w < INFINITY) || in == v || v != v) return in;
+    const bool above = v > g.hi;
+    const double t = above ? v - g.hi : g.lo - v;
+    double sh;
+    if (g.d > 0.0 && t <= g.d + g.wl) {
+        sh = t / g.q;
+        gz = g.h * sh * sh;
+    } else {
+        sh = t - g.wl > 0.0 ? t - g.wl : 0.0;
+        gz = g.w * (sh - 0.5 * g.d);
+    }
+    return above ? g.hi + sh : g.lo - sh;
+}
+
 // All trial steps in one pass; slot nu holds sum over rows of the change of
 // the FBE at w(tau_nu) relative to y, with phi = f-hat + <y, z> -
 // (lambda/2) ||R||^2 - g(z).  NUC: the largest nu_max the variant serves
 // (its accumulators, and so its register demand, scale with it).  For NAMA
 // the slot after the last trial collects ||s H xhat(s r)||^2 (backtracking
 // test 2).
+// Everything a trial needs is linear in tau: w = y + d0 + tau d1,
+// s H x(w) = h0 + tau h1 and w / lambda + s H x(w) = v0 + tau v1, so a row
+// divides twice (y / lambda, d / lambda) and not once per trial: FP64
+// arithmetic bounds this pass, the divisions were half of it.
 template <int NUC>
 __global__ void __launch_bounds__(kVB) ls_kernel(VecArgs a)
 {
@@ -380,39 +478,40 @@ __global__ void __launch_bounds__(kVB) ls_kernel(VecArgs a)
     for (int v = 0; v < NUC + 1; ++v) acc[v] = 0.0;
     FOR_BLOCK_ROWS(br, kl, k) {
         const double s = row_scale(a, br, kl);
-        const RowG rg = row_g(a, br, kl, s);
+        const RowTrial rg = row_trial(row_g(a, br, kl, s), lam);
         const double yk = a.y[k], rk = a.rp[k], dk = a.d[k];
         const double ah = s * a.hx[k];
         const double brk = nama ? s * a.hr[k] : 0.0;
         hh += brk * brk;
         const double bd = s * a.hd[k];
+        const double yl = yk / lam, lr = nama ? lam * rk : 0.0, lb = lam * brk;
         double gy;
-        (void)row_prox(yk / lam + ah, rg, lam, gy);   // g at z(y) = R + s H x
+        (void)row_prox(yl + ah, rg, gy);   // g at z(y) = R + s H x
         const double ey = yk * (rk + ah) - 0.5 * lam * rk * rk - gy;
+        const double d0 = -lr, d1 = dk + lr, g1 = bd + lb;       // w - y, s H xhat(w - y) = -lb + tau g1
+        const double h0 = ah - lb;
+        const double v0 = (yl - (nama ? rk : 0.0)) + h0, v1 = (dk / lam + (nama ? rk : 0.0)) + g1;
         double tau = 1.0;
 #pragma unroll
         for (int nu = 0; nu <= NUC; ++nu) {
             if (nu <= numax) {
-                const double cr = nama ? -(1.0 - tau) * lam : 0.0;
-                const double dl = cr * rk + tau * dk;     // w - y
-                const double hd = cr * brk + tau * bd;    // s H xhat(w - y)
-                const double w = yk + dl, hw = ah + hd;
+                const double dl = fma(tau, d1, d0);
+                const double hd = fma(tau, g1, -lb);
+                const double hw = fma(tau, g1, h0);
                 double gw;
-                const double zw = row_prox(w / lam + hw, rg, lam, gw);
+                const double zw = row_prox(fma(tau, v1, v0), rg, gw);
                 const double Rw = zw - hw;
-                acc[nu] += -ah * dl - 0.5 * dl * hd + w * zw - 0.5 * lam * Rw * Rw - gw - ey;
+                acc[nu] += (yk + dl) * zw - dl * fma(0.5, hd, ah) - 0.5 * lam * Rw * Rw - gw - ey;
             }
             tau *= 0.5;
         }
     }
-    // slots [0, kNMax) are the max-reduced ones; the sums follow them, then hh
+    // the sums follow the (unused) max slots, then hh
     double packed[kNMax + NUC + 2];
-#pragma unroll
-    for (int v = 0; v < kNMax; ++v) packed[v] = 0.0;
 #pragma unroll
     for (int v = 0; v < NUC + 2; ++v)
         packed[kNMax + v] = v <= numax ? (v < NUC + 1 ? acc[v] : 0.0) : (v == numax + 1 ? hh : 0.0);
-    block_store<kNMax + NUC + 2>(packed, kNMax + NUC + 2, a.part, a.nblocks);
+    block_store<kNMax + NUC + 2, false>(packed, a.part, a.nblocks);
 }
 
 // y+ = T(w) at the accepted step (tau = c->tau); with a.Rw kept, R(w) and
@@ -463,7 +562,7 @@ __global__ void __launch_bounds__(kVB) bt_kernel(VecArgs a)
         acc[kNMax + 0] += Rw * (s * a.hx[k] - a.hw[k]);
         acc[kNMax + 1] += Rw * Rw;
     }
-    block_store<kNMax + 2>(acc, kNMax + 2, a.part, a.nblocks);
+    block_store<kNMax + 2, false>(acc, a.part, a.nblocks);
 }
 
 // Infeasibility test, first pass: yck becomes y - yck (the change since the
@@ -505,7 +604,7 @@ __global__ void __launch_bounds__(kVB) div_kernel(VecArgs a)
         }
         a.yck[k] = a.y[k];
     }
-    block_store<kNMax + 1>(acc, kNMax + 1, a.part, a.nblocks);
+    block_store(acc, a.part, a.nblocks);
 }
 
 // GPAD update: y^{k+1} = T(w^k) = w^k - lambda R(w^k) into y (the main
@@ -532,7 +631,7 @@ __global__ void __launch_bounds__(kVB) copy_kernel(VecArgs a)
 }
 
 // ---------------------------- finalize kernels ---------------------------
-// One block per instance; lane 0 of the block takes the scalar decisions.
+// One block of kFin threads per instance; thread 0 takes the scalar decisions.
 // div_due: this update runs the infeasibility test (which then takes the
 // max_iter decision after it, as the test comes first).
 __device__ void finish_residual(Ctl *c, const double *red, int *ndone, int div_due)
@@ -556,7 +655,7 @@ __device__ void lbfgs_update(Ctl *c, const double *red)
 {
     int cnt = c->cnt, fs = c->free_slot;
     const int mem = c->mem;
-    double sg[kMemMax + 1], qg[kMemMax + 1];
+    __shared__ double sg[kMemMax + 1], qg[kMemMax + 1];
     for (int j = 0; j < cnt; ++j) {
         sg[c->order[j]] = red[PB + 6 + 5 * j + 3];
         qg[c->order[j]] = red[PB + 6 + 5 * j + 4];
@@ -605,7 +704,7 @@ __device__ void lbfgs_update(Ctl *c, const double *red)
     }
     const int n = c->order[cnt - 1];
     const double gam = c->SY[n][n] / c->QQ[n][n];
-    double u1[kMemMax], u2[kMemMax], p1[kMemMax], p2[kMemMax], t[kMemMax];
+    __shared__ double u1[kMemMax], u2[kMemMax], p1[kMemMax], p2[kMemMax], t[kMemMax];
     for (int i = 0; i < cnt; ++i) {
         u1[i] = sg[c->order[i]];
         u2[i] = gam * qg[c->order[i]];
@@ -657,28 +756,36 @@ __device__ bool halve_lambda(Ctl *c, int *ndone)
     return true;
 }
 
-__global__ void __launch_bounds__(kVB) fin_resid_kernel(Ctl *ctl, const double *part, int nblocks,
+__global__ void __launch_bounds__(kFin) fin_resid_kernel(Ctl *ctl, const double *part, int nblocks,
                                                         int with_pair, int *ndone, int div_due)
 {
-    Ctl *c = ctl + blockIdx.x;
-    if (idle(c)) return;
+    __shared__ Ctl cs;
+    ctl_copy(&cs, ctl + blockIdx.x);
+    if (idle(&cs)) return;
     __shared__ double red[kNVMax];
-    reduce_partials(part, nblocks, c->first_blk, c->nblk, with_pair ? nv_pair(c->mem) : PB, red);
-    if (threadIdx.x != 0) return;
-    finish_residual(c, red, ndone, div_due);
-    if (!c->done && with_pair) lbfgs_update(c, red);
+    reduce_partials(part, nblocks, cs.first_blk, cs.nblk, with_pair ? PB + 6 + 5 * cs.cnt : PB, red);
+    if (threadIdx.x == 0) {
+        finish_residual(&cs, red, ndone, div_due);
+        if (!cs.done && with_pair) lbfgs_update(&cs, red);
+    }
+    __syncthreads();
+    ctl_copy(ctl + blockIdx.x, &cs);
 }
 
-__global__ void __launch_bounds__(kVB) fin_grad_kernel(Ctl *ctl, const double *part, int nblocks)
+__global__ void __launch_bounds__(kFin) fin_grad_kernel(Ctl *ctl, const double *part, int nblocks)
 {
-    Ctl *c = ctl + blockIdx.x;
-    if (idle(c)) return;
+    __shared__ Ctl cs;
+    ctl_copy(&cs, ctl + blockIdx.x);
+    if (idle(&cs)) return;
     __shared__ double red[kNVMax];
-    reduce_partials(part, nblocks, c->first_blk, c->nblk, nv_pair(c->mem), red);
-    if (threadIdx.x != 0) return;
-    c->sweeps_hom++;
-    c->hh = red[R_SS];
-    lbfgs_update(c, red);
+    reduce_partials(part, nblocks, cs.first_blk, cs.nblk, PB + 6 + 5 * cs.cnt, red);
+    if (threadIdx.x == 0) {
+        cs.sweeps_hom++;
+        cs.hh = red[R_SS];
+        lbfgs_update(&cs, red);
+    }
+    __syncthreads();
+    ctl_copy(ctl + blockIdx.x, &cs);
 }
 
 // Line-search decision (the largest tau = 2^-nu with phi(w) <= phi(y), else
@@ -686,22 +793,8 @@ __global__ void __launch_bounds__(kVB) fin_grad_kernel(Ctl *ctl, const double *p
 // the iteration counter, the buffer that holds the next iterate, and the
 // flag that arms test 1 for the next update.  A skipped update (test 1
 // undid the previous one) only moves to the other buffer.
-__global__ void __launch_bounds__(kVB) fin_ls_kernel(Ctl *ctl, const double *part, int nblocks, int *ndone,
-                                                     double *trace, int trace_iters)
+__device__ void finish_line_search(Ctl *c, const double *red, int b, int *ndone, double *trace, int trace_iters)
 {
-    const int b = blockIdx.x;
-    Ctl *c = ctl + b;
-    const bool done = c->done, skip = c->skip;
-    __syncthreads();   // every thread has read the flags before lane 0 changes them
-    if (done) return;
-    if (skip) {
-        // redo = 2: the update kernel leaves y+ as it is
-        if (threadIdx.x == 0) { c->skip = 0; c->buf ^= 1; c->redo = 2; }
-        return;
-    }
-    __shared__ double red[kNVMax];
-    reduce_partials(part, nblocks, c->first_blk, c->nblk, kNMax + c->nu_max + 2, red);
-    if (threadIdx.x != 0) return;
     int acc = -1;
     for (int nu = 0; nu <= c->nu_max; ++nu) {
         const double dphi = red[kNMax + nu];
@@ -737,6 +830,30 @@ __global__ void __launch_bounds__(kVB) fin_ls_kernel(Ctl *ctl, const double *par
     c->ls_trials += acc >= 0 ? acc + 1 : c->nu_max + 1;
     c->bt_pending = c->backtrack == 1;
     c->iter++;
+}
+
+__global__ void __launch_bounds__(kFin) fin_ls_kernel(Ctl *ctl, const double *part, int nblocks, int *ndone,
+                                                     double *trace, int trace_iters)
+{
+    __shared__ Ctl cs;
+    ctl_copy(&cs, ctl + blockIdx.x);
+    if (cs.done) return;
+    if (cs.skip) {
+        // redo = 2: the update kernel leaves y+ as it is
+        if (threadIdx.x == 0) {
+            Ctl *c = ctl + blockIdx.x;
+            c->skip = 0;
+            c->buf = cs.buf ^ 1;
+            c->redo = 2;
+        }
+        return;
+    }
+    __shared__ double red[kNVMax];
+    // the max slots hold nothing here
+    reduce_partials(part, nblocks, cs.first_blk, cs.nblk, kNMax + cs.nu_max + 2, red);
+    if (threadIdx.x == 0) finish_line_search(&cs, red, blockIdx.x, ndone, trace, trace_iters);
+    __syncthreads();
+    ctl_copy(ctl + blockIdx.x, &cs);
 }
 
 // Test 1: halve lambda when <R(w), s H x(y+) - s H x(w)> > (1 - beta) ||R(w)||^2;
@@ -839,7 +956,7 @@ __global__ void __launch_bounds__(kVB) power_step_kernel(VecArgs a)
         acc[kNMax + 1] += w * w;
         a.r[k] = w;
     }
-    block_store<kNMax + 2>(acc, kNMax + 2, a.part, a.nblocks);
+    block_store<kNMax + 2, false>(acc, a.part, a.nblocks);
 }
 
 __global__ void __launch_bounds__(kVB) power_fin_kernel(Ctl *ctl, const double *part, int nblocks)
@@ -883,12 +1000,14 @@ int ensure_solver_ws(tree_factors *f, WsNeed need)
         w.buf = nullptr;
         w.bytes = 0;
     }
-    // blocks per instance: one per 1024 rows, at most 1024
+    // blocks per instance: one per 1024 rows, at most 1024; one per 256 rows (a
+    // row per thread) on handles whose rows then still fit one round of the chip
+    const int per = f->m_tot <= 2048LL * kVB ? kVB : 4 * kVB;
     std::vector<int> blk;
     w.blk_first.assign(f->ninst, 0);
     for (int b = 0; b < f->ninst; ++b) {
         const long long m = f->inst[b].m;
-        const int nb = (int)std::max<long long>(1, std::min<long long>(1024, (m + 4 * kVB - 1) / (4 * kVB)));
+        const int nb = (int)std::max<long long>(1, std::min<long long>(1024, (m + per - 1) / per));
         w.blk_first[b] = (int)(blk.size() / 3);
         for (int l = 0; l < nb; ++l) { blk.push_back(b); blk.push_back(l); blk.push_back(nb); }
     }
@@ -1041,7 +1160,7 @@ hipError_t enqueue_iteration(const tree_factors *f, const IterArgs &it, hipStrea
     a.S = w.S; a.Q = w.Qv;
     if (method == 1) {
         hipLaunchKernelGGL((resid_kernel<true, MEMCAP>), grid, blk, 0, st, a);
-        hipLaunchKernelGGL(fin_resid_kernel, fgrid, blk, 0, st, ctl, a.part, a.nblocks, 1, a.ndone, it.div_due);
+        hipLaunchKernelGGL(fin_resid_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, 1, a.ndone, it.div_due);
         if (it.div_due && (e = enqueue_div_test(f, y, st))) return e;
         VecArgs cb = a;
         cb.g = r;           // g = R
@@ -1051,14 +1170,14 @@ hipError_t enqueue_iteration(const tree_factors *f, const IterArgs &it, hipStrea
         if ((e = dual_sweep(f, 0, nullptr, r, w.d - r, hr, hd - hr, done_flags(ctl), 2, st, active))) return e;
     } else {
         hipLaunchKernelGGL((resid_kernel<false, 0>), grid, blk, 0, st, a);
-        hipLaunchKernelGGL(fin_resid_kernel, fgrid, blk, 0, st, ctl, a.part, a.nblocks, 0, a.ndone, it.div_due);
+        hipLaunchKernelGGL(fin_resid_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, 0, a.ndone, it.div_due);
         if (it.div_due && (e = enqueue_div_test(f, y, st))) return e;
         // grad phi = R + lambda s H xhat(s R)
         if ((e = dual_sweep(f, 0, nullptr, r, 0, hr, 0, done_flags(ctl), 1, st, active))) return e;
         VecArgs ga = a;
         ga.hr = hr; ga.g = g; ga.gp = gp;
         hipLaunchKernelGGL((grad_kernel<MEMCAP>), grid, blk, 0, st, ga);
-        hipLaunchKernelGGL(fin_grad_kernel, fgrid, blk, 0, st, ctl, a.part, a.nblocks);
+        hipLaunchKernelGGL(fin_grad_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks);
         VecArgs cb = a;
         cb.g = g; cb.r = w.d;
         hipLaunchKernelGGL((combine_kernel<MEMCAP>), grid, blk, 0, st, cb);
@@ -1068,7 +1187,7 @@ hipError_t enqueue_iteration(const tree_factors *f, const IterArgs &it, hipStrea
     la.method = method;
     la.y = y; la.rp = r; la.d = w.d; la.hx = w.hx; la.hr = hr; la.hd = hd; la.yn = yn;
     hipLaunchKernelGGL(ls_kernel<NUC>, grid, blk, 0, st, la);
-    hipLaunchKernelGGL(fin_ls_kernel, fgrid, blk, 0, st, ctl, a.part, a.nblocks, a.ndone, it.trace, it.trace_iters);
+    hipLaunchKernelGGL(fin_ls_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, a.ndone, it.trace, it.trace_iters);
     if (it.backtrack == 1) { la.Rw = w.Rw; la.hw = w.hw; }
     hipLaunchKernelGGL(update_kernel, grid, blk, 0, st, la);
     return hipGetLastError();
@@ -1088,7 +1207,7 @@ hipError_t enqueue_gpad(const tree_factors *f, const IterArgs &it, hipStream_t s
     if ((e = dual_sweep(f, 1, it.x0, wv, 0, w.hx, 0, done_flags(ctl), 1, st, it.active))) return e;
     a.y = wv; a.hx = w.hx; a.r = r;
     hipLaunchKernelGGL((resid_kernel<false, 0>), grid, blk, 0, st, a);
-    hipLaunchKernelGGL(fin_resid_kernel, fgrid, blk, 0, st, ctl, a.part, a.nblocks, 0, a.ndone, it.div_due);
+    hipLaunchKernelGGL(fin_resid_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, 0, a.ndone, it.div_due);
     if (it.div_due && (e = enqueue_div_test(f, wv, st))) return e;
     hipLaunchKernelGGL(fin_gpad_kernel, fgrid, dim3(64), 0, st, ctl);
     VecArgs ua = a;
