@@ -42,7 +42,13 @@ using namespace dev;
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kPanel = kRhsPanel;      // right-hand sides per launch (64)
-constexpr int kLdv = kPanel + 2;       // LDS row stride of a panel (doubles)
+// A workgroup takes RW of the launch's right-hand sides: all 64 where the
+// nodes alone fill the chip, 16 where they do not (launch_panel_any), each
+// group of 16 a workgroup of its own in blockIdx.y.  RW = 64: a tile's tasks
+// are its two halves of 32; RW = 16: one task of a single 16x16 block.
+template <int RW> constexpr int kLdv = RW + 2;            // LDS row stride of a panel (doubles)
+template <int RW> constexpr int kHalves = RW == 64 ? 2 : 1;
+template <int RW> constexpr int kBlk = RW == 16 ? 1 : 2;  // 16x16 blocks per task
 constexpr int kWg = 4;                 // wavefronts per workgroup
 constexpr int kTpwMax = 4;             // most tasks one wavefront can hold
 constexpr int kKu = 4;                 // K steps (of 4 rows) per batch of operand loads
@@ -62,10 +68,11 @@ struct Part {
 };
 
 // Tasks of a product: tiles of part 0 then part 1 (ceil(ncols/16) each),
-// two halves each; wavefront w owns tasks w, w + kWg, ...
+// kHalves each; wavefront w owns tasks w, w + kWg, ...
+template <int RW>
 struct Tasks {
     int t0, t1;                        // tiles of part 0 / part 1
-    __device__ int count() const { return 2 * (t0 + t1); }
+    __device__ int count() const { return kHalves<RW> * (t0 + t1); }
 };
 
 __host__ __device__ inline int tiles(int n) { return (n + 15) >> 4; }
@@ -98,8 +105,8 @@ __device__ __forceinline__ void stream_load(FactorStream<TPW> &f, double (&a)[kK
 // rows of D are never stored), so the loads of a batch are all in flight
 // together; only the matrix operations of unowned tasks are skipped, on a
 // wavefront-uniform test.
-template <int TPW>
-__device__ __forceinline__ void stream_open(FactorStream<TPW> &f, const Part (&p)[2], const Tasks &tk, int R,
+template <int TPW, int RW>
+__device__ __forceinline__ void stream_open(FactorStream<TPW> &f, const Part (&p)[2], const Tasks<RW> &tk, int R,
                                             int wave, int lane)
 {
     const int n = tk.count();
@@ -108,7 +115,7 @@ __device__ __forceinline__ void stream_open(FactorStream<TPW> &f, const Part (&p
     for (int s = 0; s < TPW; ++s) {
         const int task = wave + kWg * s;
         f.own[s] = task < n;
-        const int tile = (f.own[s] ? task : 0) >> 1;
+        const int tile = (f.own[s] ? task : 0) / kHalves<RW>;
         const int part = tile < tk.t0 ? 0 : 1;
         const int c = (part ? tile - tk.t0 : tile) * 16 + lc;
         f.ap[s] = p[part].M + p[part].col0 + (c < p[part].ncols ? c : 0) + (long long)lr * p[part].ld;
@@ -123,31 +130,31 @@ __device__ __forceinline__ void stream_open(FactorStream<TPW> &f, const Part (&p
 // batch issued before the matrix operations of the current one (two register
 // buffers); the last R mod 16 rows are a tail whose rows past R read a valid
 // row and are zeroed (the panel needs no padding rows).
-template <int TPW>
-__device__ __forceinline__ void stream_run(FactorStream<TPW> &f, int R, const double *V, v4d (&acc)[TPW][2],
+template <int RW, int TPW>
+__device__ __forceinline__ void stream_run(FactorStream<TPW> &f, int R, const double *V, v4d (&acc)[TPW][kBlk<RW>],
                                            int wave, int lane)
 {
+    constexpr int NB = kBlk<RW>, ldv = kLdv<RW>;
     const int lr = lane >> 4, lc = lane & 15;
-    const double *vb = V + lr * kLdv + (wave & 1) * 32 + lc;   // this lane's B entry of row lr
-    auto mma = [&](const double (&a)[kKu][TPW], const double (&b)[kKu][2]) {
+    const double *vb = V + lr * ldv + (kHalves<RW> == 2 ? (wave & 1) * 32 : 0) + lc;   // this lane's B entry of row lr
+    auto mma = [&](const double (&a)[kKu][TPW], const double (&b)[kKu][NB]) {
 #pragma unroll
         for (int u = 0; u < kKu; ++u)
 #pragma unroll
             for (int s = 0; s < TPW; ++s)
-                if (f.own[s]) {
-                    acc[s][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][s], b[u][0], acc[s][0], 0, 0, 0);
-                    acc[s][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][s], b[u][1], acc[s][1], 0, 0, 0);
-                }
-    };
-    auto bload = [&](double (&b)[kKu][2], int k0) {
+                if (f.own[s])
 #pragma unroll
-        for (int u = 0; u < kKu; ++u) {
-            b[u][0] = vb[(k0 + 4 * u) * kLdv];
-            b[u][1] = vb[(k0 + 4 * u) * kLdv + 16];
-        }
+                    for (int h = 0; h < NB; ++h)
+                        acc[s][h] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][s], b[u][h], acc[s][h], 0, 0, 0);
+    };
+    auto bload = [&](double (&b)[kKu][NB], int k0) {
+#pragma unroll
+        for (int u = 0; u < kKu; ++u)
+#pragma unroll
+            for (int h = 0; h < NB; ++h) b[u][h] = vb[(k0 + 4 * u) * ldv + 16 * h];
     };
     const int nfull = R / (4 * kKu);
-    double a1[kKu][TPW], b[kKu][2];
+    double a1[kKu][TPW], b[kKu][NB];
     int q = 0;
     for (; q + 2 <= nfull; q += 2) {
         stream_load(f, a1);
@@ -174,29 +181,33 @@ __device__ __forceinline__ void stream_run(FactorStream<TPW> &f, int R, const do
                 const double v = f.ap[s][d * f.ld[s]];
                 f.a0[u][s] = in ? v : 0.0;
             }
-            const double v0 = vb[(k0 + d) * kLdv], v1 = vb[(k0 + d) * kLdv + 16];
-            b[u][0] = in ? v0 : 0.0;
-            b[u][1] = in ? v1 : 0.0;
+#pragma unroll
+            for (int h = 0; h < NB; ++h) {
+                const double v0 = vb[(k0 + d) * ldv + 16 * h];
+                b[u][h] = in ? v0 : 0.0;
+            }
         }
         mma(f.a0, b);    // the steps past R add zero products
     }
 }
 
 
-template <int TPW>
-__device__ __forceinline__ void product(const Part (&p)[2], const Tasks &tk, int R, const double *V,
-                                        v4d (&acc)[TPW][2], int wave, int lane)
+template <int RW, int TPW>
+__device__ __forceinline__ void product(const Part (&p)[2], const Tasks<RW> &tk, int R, const double *V,
+                                        v4d (&acc)[TPW][kBlk<RW>], int wave, int lane)
 {
     FactorStream<TPW> f;
     stream_open(f, p, tk, R, wave, lane);
-    stream_run(f, R, V, acc, wave, lane);
+    stream_run<RW>(f, R, V, acc, wave, lane);
 }
 
-template <int TPW>
-__device__ __forceinline__ void zero(v4d (&acc)[TPW][2])
+template <int TPW, int NB>
+__device__ __forceinline__ void zero(v4d (&acc)[TPW][NB])
 {
 #pragma unroll
-    for (int s = 0; s < TPW; ++s) acc[s][0] = acc[s][1] = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int s = 0; s < TPW; ++s)
+#pragma unroll
+        for (int h = 0; h < NB; ++h) acc[s][h] = v4d{0.0, 0.0, 0.0, 0.0};
 }
 
 // Position of element (s, h, e) of this lane's results: part, row within the
@@ -207,15 +218,16 @@ struct Slot {
     bool valid;
 };
 
-__device__ __forceinline__ Slot slot(const Tasks &tk, const int (&ncols)[2], int s, int h, int e, int wave,
+template <int RW>
+__device__ __forceinline__ Slot slot(const Tasks<RW> &tk, const int (&ncols)[2], int s, int h, int e, int wave,
                                      int lane)
 {
     Slot o;
     const int task = wave + kWg * s;
-    const int tile = task >> 1;
+    const int tile = task / kHalves<RW>;
     o.part = tile < tk.t0 ? 0 : 1;
     o.row = (o.part ? tile - tk.t0 : tile) * 16 + (lane >> 4) + 4 * e;
-    o.rhs = (task & 1) * 32 + h * 16 + (lane & 15);
+    o.rhs = (kHalves<RW> == 2 ? (task & 1) * 32 : 0) + h * 16 + (lane & 15);
     o.valid = task < tk.count() && o.row < ncols[o.part];
     return o;
 }
@@ -224,22 +236,22 @@ __device__ __forceinline__ Slot slot(const Tasks &tk, const int (&ncols)[2], int
 // panel rows [r0, r0 + n): V[r0 + r][k] = src(k, r).  A wavefront reads one
 // right-hand side per instruction (consecutive rows on consecutive lanes),
 // all its loads issued before the first LDS write.
-template <typename Src>
+template <int RW, typename Src>
 __device__ __forceinline__ void stage(double *V, int r0, int n, Src src)
 {
-    constexpr int Q = 8;               // right-hand sides per round (loads in flight per lane)
+    constexpr int Q = RW / kWg < 8 ? RW / kWg : 8;   // right-hand sides per round (loads in flight per lane)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
     for (int rb = 0; rb < n; rb += kWave) {
         const int r = rb + lane;
         const bool in = r < n;
         const int rc = in ? r : n - 1;     // lanes past n read a valid entry and store nothing
-        for (int k0 = wave; k0 < kPanel; k0 += Q * kWg) {
+        for (int k0 = wave; k0 < RW; k0 += Q * kWg) {
             double v[Q];
 #pragma unroll
             for (int q = 0; q < Q; ++q) v[q] = src(k0 + kWg * q, rc);
             if (in) {
 #pragma unroll
-                for (int q = 0; q < Q; ++q) V[(r0 + r) * kLdv + k0 + kWg * q] = v[q];
+                for (int q = 0; q < Q; ++q) V[(r0 + r) * kLdv<RW> + k0 + kWg * q] = v[q];
             }
         }
     }
@@ -253,16 +265,16 @@ __device__ __forceinline__ void stage(double *V, int r0, int n, Src src)
 // first factor batch, so they end as sum A'qhat + s_i y^x + chat_i (rows
 // [0, nx), completed to qhat_i after the second product) and g_i (rows
 // [nx, nx + nu), the input of the second product).
-template <int TPW>
+template <int TPW, int RW>
 __device__ void bwd_node64(const SweepArgs &a, const InstDesc &I, int i, double *V, bool child_in_lds,
                            bool store_q, int wave, int lane)
 {
     const int nx = I.nx, nu = I.nu;
     const int *cp = a.cp + I.cp;
-    const Tasks tk{tiles(nx), tiles(nu)};
+    const Tasks<RW> tk{tiles(nx), tiles(nu)};
     const int ncols[2] = {nx, nu};
     const double si = a.sc ? a.sc[I.sc + i] : 1.0;
-    v4d S[TPW][2];
+    v4d S[TPW][kBlk<RW>];
     {
         // rows past a part read its last row; slots of unowned tasks are never stored
         const double *ch = a.chat + I.chat + (long long)i * nx;
@@ -271,7 +283,7 @@ __device__ void bwd_node64(const SweepArgs &a, const InstDesc &I, int i, double 
 #pragma unroll
         for (int s = 0; s < TPW; ++s)
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int h = 0; h < kBlk<RW>; ++h)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const Slot o = slot(tk, ncols, s, h, e, wave, lane);
@@ -282,7 +294,7 @@ __device__ void bwd_node64(const SweepArgs &a, const InstDesc &I, int i, double 
 #pragma unroll
             for (int s = 0; s < TPW; ++s)
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
+                for (int h = 0; h < kBlk<RW>; ++h)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const Slot o = slot(tk, ncols, s, h, e, wave, lane);
@@ -297,18 +309,18 @@ __device__ void bwd_node64(const SweepArgs &a, const InstDesc &I, int i, double 
                 const double sj = a.sc ? a.sc[I.sc + j] : 1.0;
                 const double *cj = a.chat + I.chat + (long long)j * nx;
                 if (a.affine)
-                    stage(V, 0, nx,
+                    stage<RW>(V, 0, nx,
                           [&](int k, int r) { return sj * y_ptr(a, I, k, j)[r] + cj[k * a.chat_rs + r]; });
                 else
-                    stage(V, 0, nx, [&](int k, int r) { return sj * y_ptr(a, I, k, j)[r]; });
+                    stage<RW>(V, 0, nx, [&](int k, int r) { return sj * y_ptr(a, I, k, j)[r]; });
             } else {
-                stage(V, 0, nx, [&](int k, int r) { return qhat_ptr(a, I, k, j)[r]; });
+                stage<RW>(V, 0, nx, [&](int k, int r) { return qhat_ptr(a, I, k, j)[r]; });
             }
             __syncthreads();
         }
         const double *Mb = a.Mb + I.Mb + (long long)j * nx * I.ldM;
         const Part p[2] = {{Mb, I.ldM, 0, nx}, {Mb, I.ldM, nx, nu}};
-        product(p, tk, nx, V, S, wave, lane);
+        product<RW>(p, tk, nx, V, S, wave, lane);
         if (j + 1 < cp[i + 1]) __syncthreads();   // every wavefront is done with the child panel
     }
     // first batch of [K' ; -R~^{-1}] in flight across the barriers
@@ -322,22 +334,22 @@ __device__ void bwd_node64(const SweepArgs &a, const InstDesc &I, int i, double 
 #pragma unroll
     for (int s = 0; s < TPW; ++s)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < kBlk<RW>; ++h)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const Slot o = slot(tk, ncols, s, h, e, wave, lane);
-                if (o.valid) V[(o.part ? nx + o.row : o.row) * kLdv + o.rhs] = S[s][h][e];
+                if (o.valid) V[(o.part ? nx + o.row : o.row) * kLdv<RW> + o.rhs] = S[s][h][e];
             }
     __syncthreads();
     // [K' g ; -R~^{-1} g]
-    v4d T[TPW][2];
+    v4d T[TPW][kBlk<RW>];
     zero(T);
-    stream_run(f2, nu, V + nx * kLdv, T, wave, lane);
+    stream_run<RW>(f2, nu, V + nx * kLdv<RW>, T, wave, lane);
     // each lane completes its own entries of rows [0, nx); the g rows are not written
 #pragma unroll
     for (int s = 0; s < TPW; ++s)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < kBlk<RW>; ++h)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const Slot o = slot(tk, ncols, s, h, e, wave, lane);
@@ -345,8 +357,8 @@ __device__ void bwd_node64(const SweepArgs &a, const InstDesc &I, int i, double 
                 if (o.part == 1) {
                     kbuf_ptr(a, I, o.rhs, i)[o.row] = T[s][h][e];
                 } else {
-                    const double q = V[o.row * kLdv + o.rhs] + T[s][h][e];
-                    V[o.row * kLdv + o.rhs] = q;
+                    const double q = V[o.row * kLdv<RW> + o.rhs] + T[s][h][e];
+                    V[o.row * kLdv<RW> + o.rhs] = q;
                     if (store_q) qhat_ptr(a, I, o.rhs, i)[o.row] = q;
                 }
             }
@@ -358,55 +370,55 @@ __device__ void bwd_node64(const SweepArgs &a, const InstDesc &I, int i, double 
 // replaces x_i in the panel.  The accumulators start at k_i (for u_i = K_i x_i
 // + k_i) and at c_j (for x_j = A_j x_i + B_j u_i + c_j), loaded with the first
 // factor batch.
-template <int TPW>
+template <int TPW, int RW>
 __device__ void fwd_node64(const SweepArgs &a, const InstDesc &I, int i, double *V, bool keep_child, int wave,
                            int lane)
 {
     const int nx = I.nx, nu = I.nu, W = nx + nu;
     const int *cp = a.cp + I.cp;
     const int ncols[2] = {nx, nu};
-    const Tasks tkx{tiles(nx), 0};
+    const Tasks<RW> tkx{tiles(nx), 0};
     const int j0 = cp[i], j1 = cp[i + 1];
     FactorStream<TPW> fx;     // the first child's [A B], opened before the u_i barrier
     {
-        const Tasks tk{0, tiles(nu)};
-        v4d U[TPW][2];
+        const Tasks<RW> tk{0, tiles(nu)};
+        v4d U[TPW][kBlk<RW>];
         // rows past nu read row nu - 1; slots of unowned tasks are never stored
 #pragma unroll
         for (int s = 0; s < TPW; ++s)
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int h = 0; h < kBlk<RW>; ++h)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const Slot o = slot(tk, ncols, s, h, e, wave, lane);
                     U[s][h][e] = kbuf_ptr(a, I, o.rhs, i)[o.row < nu ? o.row : nu - 1];
                 }
         const Part p[2] = {{nullptr, 0, 0, 0}, {a.Kf + I.Kf + (long long)i * nx * I.ldu, I.ldu, 0, nu}};
-        product(p, tk, nx, V, U, wave, lane);
+        product<RW>(p, tk, nx, V, U, wave, lane);
         // rows [nx, W) are not read by K x_i: u_i goes there directly
 #pragma unroll
         for (int s = 0; s < TPW; ++s)
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int h = 0; h < kBlk<RW>; ++h)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const Slot o = slot(tk, ncols, s, h, e, wave, lane);
                     if (!o.valid) continue;
                     u_ptr(a, I, o.rhs, i)[o.row] = U[s][h][e];
-                    V[(nx + o.row) * kLdv + o.rhs] = U[s][h][e];
+                    V[(nx + o.row) * kLdv<RW> + o.rhs] = U[s][h][e];
                 }
         const Part px[2] = {{a.Mf + I.Mf + (long long)j0 * W * I.ldx, I.ldx, 0, nx}, {nullptr, 0, 0, 0}};
         stream_open(fx, px, tkx, W, wave, lane);
         __syncthreads();
     }
-    v4d X[TPW][2];
+    v4d X[TPW][kBlk<RW>];
     for (int j = j0; j < j1; ++j) {
         if (a.affine) {
             const double *cj = a.cvec + I.c + (long long)j * nx;
 #pragma unroll
             for (int s = 0; s < TPW; ++s)
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
+                for (int h = 0; h < kBlk<RW>; ++h)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const Slot o = slot(tkx, ncols, s, h, e, wave, lane);
@@ -419,11 +431,11 @@ __device__ void fwd_node64(const SweepArgs &a, const InstDesc &I, int i, double 
             const Part p[2] = {{a.Mf + I.Mf + (long long)j * W * I.ldx, I.ldx, 0, nx}, {nullptr, 0, 0, 0}};
             stream_open(fx, p, tkx, W, wave, lane);
         }
-        stream_run(fx, W, V, X, wave, lane);
+        stream_run<RW>(fx, W, V, X, wave, lane);
 #pragma unroll
         for (int s = 0; s < TPW; ++s)
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int h = 0; h < kBlk<RW>; ++h)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const Slot o = slot(tkx, ncols, s, h, e, wave, lane);
@@ -435,11 +447,11 @@ __device__ void fwd_node64(const SweepArgs &a, const InstDesc &I, int i, double 
 #pragma unroll
         for (int s = 0; s < TPW; ++s)
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int h = 0; h < kBlk<RW>; ++h)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const Slot o = slot(tkx, ncols, s, h, e, wave, lane);
-                    if (o.valid) V[o.row * kLdv + o.rhs] = X[s][h][e];
+                    if (o.valid) V[o.row * kLdv<RW> + o.rhs] = X[s][h][e];
                 }
         __syncthreads();
     }
@@ -447,56 +459,78 @@ __device__ void fwd_node64(const SweepArgs &a, const InstDesc &I, int i, double 
 
 // x_i into panel rows [0, nx): x0 at the root (also written to the output),
 // else the values the previous stage stored.
+template <int RW>
 __device__ void load_x64(const SweepArgs &a, const InstDesc &I, int i, double *V)
 {
     const int nx = I.nx;
     if (i != 0) {
-        stage(V, 0, nx, [&](int k, int r) { return x_ptr(a, I, k, i)[r]; });
+        stage<RW>(V, 0, nx, [&](int k, int r) { return x_ptr(a, I, k, i)[r]; });
     } else if (a.affine) {
-        stage(V, 0, nx, [&](int k, int r) { return a.x0[k * a.x0_rs + I.x0 + r]; });
+        stage<RW>(V, 0, nx, [&](int k, int r) { return a.x0[k * a.x0_rs + I.x0 + r]; });
         __syncthreads();
         // the root's x is x0: written out too (lanes past nx store nothing)
-        for (int k = threadIdx.x / kWave; k < kPanel; k += kWg)
-            for (int r = threadIdx.x & (kWave - 1); r < nx; r += kWave) x_ptr(a, I, k, 0)[r] = V[r * kLdv + k];
+        for (int k = threadIdx.x / kWave; k < RW; k += kWg)
+            for (int r = threadIdx.x & (kWave - 1); r < nx; r += kWave) x_ptr(a, I, k, 0)[r] = V[r * kLdv<RW> + k];
     } else {
-        stage(V, 0, nx, [&](int k, int r) { return 0.0; });
-        for (int k = threadIdx.x / kWave; k < kPanel; k += kWg)
+        stage<RW>(V, 0, nx, [&](int k, int r) { return 0.0; });
+        for (int k = threadIdx.x / kWave; k < RW; k += kWg)
             for (int r = threadIdx.x & (kWave - 1); r < nx; r += kWave) x_ptr(a, I, k, 0)[r] = 0.0;
     }
     __syncthreads();
 }
 
+// The arguments of this workgroup's group of right-hand sides (blockIdx.y).
+template <int RW>
+__device__ __forceinline__ void take_group(SweepArgs &a)
+{
+    if constexpr (RW < kPanel) {
+        const long long g = (long long)blockIdx.y * RW;
+        a.y += g * a.y_rs;
+        a.xo += g * a.xo_rs;
+        if (a.uo) a.uo += g * a.uo_rs;
+        if (a.x0) a.x0 += g * a.x0_rs;
+        a.qhat += g * a.qhat_rs;
+        a.kbuf += g * a.kbuf_rs;
+        a.chat += g * a.chat_rs;
+        a.cvec += g * a.c_rs;
+        if (a.panel_done) a.done += g * a.done_stride;
+    }
+}
+
 // A workgroup leaves at once when its instance has finished or, on a shared
 // panel, when every copy of the panel has (one flag per lane; the same
 // answer in every wavefront).
+template <int RW>
 __device__ __forceinline__ bool panel_skipped(const SweepArgs &a, int inst)
 {
     if (!a.panel_done) return skipped(a, inst);
-    const int lane = threadIdx.x & (kWave - 1);
+    const int lane = threadIdx.x & (RW - 1);
     return __all(a.done[(long long)lane * a.done_stride] != 0);
 }
 
-template <int TPW>
+template <int TPW, int RW>
 __global__ void __launch_bounds__(kWave *kWg, kMinWavesBwd<TPW>) bwd_trunk64_kernel(SweepArgs a)
 {
+    take_group<RW>(a);
     extern __shared__ double lds[];
     const Item it = a.items[blockIdx.x];
-    if (panel_skipped(a, it.inst)) return;
+    if (panel_skipped<RW>(a, it.inst)) return;
     const InstDesc I = a.inst[it.inst];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
-    bwd_node64<TPW>(a, I, it.idx, lds, false, true, wave, lane);
+    bwd_node64<TPW, RW>(a, I, it.idx, lds, false, true, wave, lane);
 }
 
-template <int TPW>
+template <int TPW, int RW>
 __global__ void __launch_bounds__(kWave *kWg, kMinWavesFwd<TPW>) fwd_trunk64_kernel(SweepArgs a)
 {
+    take_group<RW>(a);
     extern __shared__ double lds[];
     const Item it = a.items[blockIdx.x];
-    if (panel_skipped(a, it.inst)) return;
+    if (panel_skipped<RW>(a, it.inst)) return;
     const InstDesc I = a.inst[it.inst];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
-    load_x64(a, I, it.idx, lds);
-    fwd_node64<TPW>(a, I, it.idx, lds, false, wave, lane);
+    load_x64<RW>(a, I, it.idx, lds);
+    fwd_node64<TPW, RW>(a, I, it.idx, lds, false, wave, lane);
 }
 
 // The lane and wavefront ids as values the compiler cannot see through: the
@@ -510,36 +544,38 @@ __device__ __forceinline__ void opaque_ids(int &wave, int &lane)
 }
 
 // Chains below s*: one workgroup per chain (items: instance, chain).
-template <int TPW>
+template <int TPW, int RW>
 __global__ void __launch_bounds__(kWave *kWg, kMinWavesBwd<TPW>) bwd_chain64_kernel(SweepArgs a)
 {
+    take_group<RW>(a);
     extern __shared__ double lds[];
     const Item it = a.items[blockIdx.x];
-    if (panel_skipped(a, it.inst)) return;
+    if (panel_skipped<RW>(a, it.inst)) return;
     const InstDesc I = a.inst[it.inst];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
     const int *sp = a.sp + I.sp;
     for (int t = I.N - 1; t >= I.sstar; --t) {
         int w = wave, l = lane;
         opaque_ids(w, l);
-        bwd_node64<TPW>(a, I, sp[t] + it.idx, lds, t != I.N - 1, t == I.sstar && t > 0, w, l);
+        bwd_node64<TPW, RW>(a, I, sp[t] + it.idx, lds, t != I.N - 1, t == I.sstar && t > 0, w, l);
     }
 }
 
-template <int TPW>
+template <int TPW, int RW>
 __global__ void __launch_bounds__(kWave *kWg, kMinWavesFwd<TPW>) fwd_chain64_kernel(SweepArgs a)
 {
+    take_group<RW>(a);
     extern __shared__ double lds[];
     const Item it = a.items[blockIdx.x];
-    if (panel_skipped(a, it.inst)) return;
+    if (panel_skipped<RW>(a, it.inst)) return;
     const InstDesc I = a.inst[it.inst];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
     const int *sp = a.sp + I.sp;
-    load_x64(a, I, sp[I.sstar] + it.idx, lds);
+    load_x64<RW>(a, I, sp[I.sstar] + it.idx, lds);
     for (int t = I.sstar; t < I.N; ++t) {
         int w = wave, l = lane;
         opaque_ids(w, l);
-        fwd_node64<TPW>(a, I, sp[t] + it.idx, lds, t + 1 < I.N, w, l);
+        fwd_node64<TPW, RW>(a, I, sp[t] + it.idx, lds, t + 1 < I.N, w, l);
     }
 }
 
@@ -569,46 +605,73 @@ static int panel_tpw_fwd(const tree_factors *f)
     return t;
 }
 
-// TB tasks per wavefront in the backward kernels, TF in the forward ones.
-template <int TB, int TF>
-static void launch_panel(const tree_factors *f, const SweepArgs &a, size_t lds, hipStream_t st)
+// One launch over n nodes or chains: RW right-hand sides per workgroup.
+template <int TB, int TF, int RW>
+static void launch_panel_part(bool backward, bool chain, const SweepArgs &a, int rows, hipStream_t st)
 {
-    const dim3 blk(kWave * kWg);
+    const dim3 grid(a.nitems, kPanel / RW), blk(kWave * kWg);
+    const size_t lds = sizeof(double) * (size_t)rows * kLdv<RW>;
+    if (chain && backward) hipLaunchKernelGGL((bwd_chain64_kernel<TB, RW>), grid, blk, lds, st, a);
+    else if (chain) hipLaunchKernelGGL((fwd_chain64_kernel<TF, RW>), grid, blk, lds, st, a);
+    else if (backward) hipLaunchKernelGGL((bwd_trunk64_kernel<TB, RW>), grid, blk, lds, st, a);
+    else hipLaunchKernelGGL((fwd_trunk64_kernel<TF, RW>), grid, blk, lds, st, a);
+}
+
+// Fewest nodes (chains) of a launch that take 64 right-hand sides per workgroup.
+// Below, a workgroup per node leaves most of the chip idle and each of its
+// steps waits out its own memory latencies: four workgroups of 16 right-hand
+// sides hide them in one another, for four times the (cached) factor reads.
+// 64 copies, ms per sweep with every launch at 64 / at 16: 243 chains of 10
+// stages, nx=20, nu=10 (35 sweeps of a NAMA solve) 14.5 / 11.9 in all; 400
+// scenarios, nx=40, nu=20 0.273 / 0.267; 450, nx=64, nu=32 0.376 / 0.395, nx=20,
+// nu=10 0.201 / 0.217; 1,024, nx=64, nu=32 1.07 with every launch at 64, 1.35 at
+// 16 and 0.91 with this rule.
+// (Groups of 32 were never the best of the three by more than 1%.)
+constexpr int kNodes64 = 416;
+
+// TB tasks per wavefront in the backward kernels, TF in the forward ones at 64
+// right-hand sides per workgroup; half as many at 16.
+template <int TB, int TF>
+static void launch_panel_any(bool backward, bool chain, const SweepArgs &a, int rows, hipStream_t st)
+{
+    constexpr int HB = (TB + 1) / 2, HF = (TF + 1) / 2;
+    if (a.nitems >= kNodes64) launch_panel_part<TB, TF, 64>(backward, chain, a, rows, st);
+    else launch_panel_part<HB, HF, 16>(backward, chain, a, rows, st);
+}
+
+template <int TB, int TF>
+static void launch_panel(const tree_factors *f, const SweepArgs &a, int rows, hipStream_t st)
+{
     SweepArgs ca = a;
     ca.items = f->panel_chain_items;
     ca.nitems = f->npanel_chain_items;
     const std::vector<LevelPlan> &levels = f->shared > 1 ? f->panel_levels : f->levels;
-    if (ca.nitems > 0) hipLaunchKernelGGL(bwd_chain64_kernel<TB>, dim3(ca.nitems), blk, lds, st, ca);
-    for (int k = (int)levels.size() - 1; k >= 0; --k) {
+    auto level = [&](bool backward, const LevelPlan &lv) {
         SweepArgs la = a;
-        la.items = levels[k].items;
-        la.nitems = levels[k].count;
-        if (la.nitems > 0) hipLaunchKernelGGL(bwd_trunk64_kernel<TB>, dim3(la.nitems), blk, lds, st, la);
-    }
-    for (size_t k = 0; k < levels.size(); ++k) {
-        SweepArgs la = a;
-        la.items = levels[k].items;
-        la.nitems = levels[k].count;
-        if (la.nitems > 0) hipLaunchKernelGGL(fwd_trunk64_kernel<TF>, dim3(la.nitems), blk, lds, st, la);
-    }
-    if (ca.nitems > 0) hipLaunchKernelGGL(fwd_chain64_kernel<TF>, dim3(ca.nitems), blk, lds, st, ca);
+        la.items = lv.items;
+        la.nitems = lv.count;
+        if (la.nitems > 0) launch_panel_any<TB, TF>(backward, false, la, rows, st);
+    };
+    if (ca.nitems > 0) launch_panel_any<TB, TF>(true, true, ca, rows, st);
+    for (int k = (int)levels.size() - 1; k >= 0; --k) level(true, levels[k]);
+    for (size_t k = 0; k < levels.size(); ++k) level(false, levels[k]);
+    if (ca.nitems > 0) launch_panel_any<TB, TF>(false, true, ca, rows, st);
 }
 
 hipError_t launch_panel_sweep(const tree_factors *f, const SweepArgs &a, hipStream_t st)
 {
     int W = 2;
     for (const InstDesc &I : f->inst) W = W > I.nx + I.nu ? W : I.nx + I.nu;
-    const size_t lds = sizeof(double) * (size_t)W * kLdv;
     const int tb = panel_tpw(f), tf = panel_tpw_fwd(f);
     switch (tb * 8 + tf) {
-    case 1 * 8 + 1: launch_panel<1, 1>(f, a, lds, st); break;
-    case 2 * 8 + 1: launch_panel<2, 1>(f, a, lds, st); break;
-    case 2 * 8 + 2: launch_panel<2, 2>(f, a, lds, st); break;
-    case 3 * 8 + 2: launch_panel<3, 2>(f, a, lds, st); break;
-    case 3 * 8 + 3: launch_panel<3, 3>(f, a, lds, st); break;
-    case 4 * 8 + 2: launch_panel<4, 2>(f, a, lds, st); break;
-    case 4 * 8 + 3: launch_panel<4, 3>(f, a, lds, st); break;
-    case 4 * 8 + 4: launch_panel<4, 4>(f, a, lds, st); break;
+    case 1 * 8 + 1: launch_panel<1, 1>(f, a, W, st); break;
+    case 2 * 8 + 1: launch_panel<2, 1>(f, a, W, st); break;
+    case 2 * 8 + 2: launch_panel<2, 2>(f, a, W, st); break;
+    case 3 * 8 + 2: launch_panel<3, 2>(f, a, W, st); break;
+    case 3 * 8 + 3: launch_panel<3, 3>(f, a, W, st); break;
+    case 4 * 8 + 2: launch_panel<4, 2>(f, a, W, st); break;
+    case 4 * 8 + 3: launch_panel<4, 3>(f, a, W, st); break;
+    case 4 * 8 + 4: launch_panel<4, 4>(f, a, W, st); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
