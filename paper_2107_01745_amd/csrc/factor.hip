@@ -669,6 +669,8 @@ void free_tree(tree_factors *f)
                     (void *)f->map_ws})
         if (p) (void)hipFree(p);
     if (f->d_inst_xu && f->d_inst_xu != f->d_inst) (void)hipFree(f->d_inst_xu);
+    if (f->sws.ndone_host) (void)hipHostFree(f->sws.ndone_host);
+    if (f->sws.polled) (void)hipEventDestroy(f->sws.polled);
     for (auto &cp : f->chains)
         if (cp.items) (void)hipFree(cp.items);
     for (auto &lv : f->levels) free_level(lv);

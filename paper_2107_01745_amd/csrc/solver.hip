@@ -8,7 +8,8 @@
 // Every iteration is a fixed sequence of kernels on the caller's stream; all
 // scalars (residual norms, curvature test, L-BFGS coefficients, the accepted
 // step) are reduced and decided on the device by single-block "finalize"
-// kernels, so the host only reads a stop flag every check_every iterations.
+// kernels, so the host only reads a stop flag every check_every iterations,
+// with the next iteration already queued.
 // Once the flag is set every remaining kernel returns immediately.
 //
 // Vector passes (grid-stride over the m dual rows, row r of node i scaled by
@@ -1117,8 +1118,9 @@ struct IterArgs {
 
 // Infeasibility test of the iterate y (after fin_resid): the change since
 // the last test, its homogeneous sweep into hd, the reductions and the
-// decision.
-hipError_t enqueue_div_test(const tree_factors *f, const double *y, hipStream_t st)
+// decision.  first: no instance has an earlier iterate yet, this one is only
+// kept (no change to sweep).
+hipError_t enqueue_div_test(const tree_factors *f, const double *y, bool first, hipStream_t st)
 {
     const SolverWS &w = f->sws;
     VecArgs a = vec_args(f);
@@ -1127,9 +1129,11 @@ hipError_t enqueue_div_test(const tree_factors *f, const double *y, hipStream_t 
     double *hd = w.hr2 + f->m_tot;
     a.y = y; a.hx = w.hx; a.hd = hd;
     hipLaunchKernelGGL(div_prep_kernel, grid, blk, 0, st, a);
-    hipError_t e = dual_sweep(f, 0, nullptr, w.yck, 0, hd, 0, div_flags(ctl), 1, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(div_kernel, grid, blk, 0, st, a);
+    if (!first) {
+        hipError_t e = dual_sweep(f, 0, nullptr, w.yck, 0, hd, 0, div_flags(ctl), 1, st);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(div_kernel, grid, blk, 0, st, a);
+    }
     hipLaunchKernelGGL(fin_div_kernel, fgrid, blk, 0, st, ctl, a.part, a.nblocks, a.ndone);
     return hipGetLastError();
 }
@@ -1161,7 +1165,7 @@ hipError_t enqueue_iteration(const tree_factors *f, const IterArgs &it, hipStrea
     if (method == 1) {
         hipLaunchKernelGGL((resid_kernel<true, MEMCAP>), grid, blk, 0, st, a);
         hipLaunchKernelGGL(fin_resid_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, 1, a.ndone, it.div_due);
-        if (it.div_due && (e = enqueue_div_test(f, y, st))) return e;
+        if (it.div_due && (e = enqueue_div_test(f, y, k == 0, st))) return e;
         VecArgs cb = a;
         cb.g = r;           // g = R
         cb.r = w.d;         // output direction
@@ -1171,7 +1175,7 @@ hipError_t enqueue_iteration(const tree_factors *f, const IterArgs &it, hipStrea
     } else {
         hipLaunchKernelGGL((resid_kernel<false, 0>), grid, blk, 0, st, a);
         hipLaunchKernelGGL(fin_resid_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, 0, a.ndone, it.div_due);
-        if (it.div_due && (e = enqueue_div_test(f, y, st))) return e;
+        if (it.div_due && (e = enqueue_div_test(f, y, k == 0, st))) return e;
         // grad phi = R + lambda s H xhat(s R)
         if ((e = dual_sweep(f, 0, nullptr, r, 0, hr, 0, done_flags(ctl), 1, st, active))) return e;
         VecArgs ga = a;
@@ -1208,7 +1212,7 @@ hipError_t enqueue_gpad(const tree_factors *f, const IterArgs &it, hipStream_t s
     a.y = wv; a.hx = w.hx; a.r = r;
     hipLaunchKernelGGL((resid_kernel<false, 0>), grid, blk, 0, st, a);
     hipLaunchKernelGGL(fin_resid_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, 0, a.ndone, it.div_due);
-    if (it.div_due && (e = enqueue_div_test(f, wv, st))) return e;
+    if (it.div_due && (e = enqueue_div_test(f, wv, it.k == 0, st))) return e;
     hipLaunchKernelGGL(fin_gpad_kernel, fgrid, dim3(64), 0, st, ctl);
     VecArgs ua = a;
     ua.g = wv; ua.r = r; ua.yn = ym;
@@ -1317,6 +1321,8 @@ int solve(const tree_factors *fc, const double *x0, const solver_opts *opts_in, 
     int rc = ensure_solver_ws(f, WsNeed{o.mem, method == 0, div_window > 0, backtrack == 1});
     if (rc) return rc;
     if ((rc = ensure_sweep_ws(f, 2))) return rc;
+    if (!f->sws.ndone_host) STOTREE_HIP(hipHostMalloc(reinterpret_cast<void **>(&f->sws.ndone_host), sizeof(int), 0));
+    if (!f->sws.polled) STOTREE_HIP(hipEventCreateWithFlags(&f->sws.polled, hipEventDisableTiming));
     const SolverWS &w = f->sws;
     Ctl *dctl = reinterpret_cast<Ctl *>(w.ctl);
     std::vector<Ctl> h = fresh_ctl(f);
@@ -1353,18 +1359,36 @@ int solve(const tree_factors *fc, const double *x0, const solver_opts *opts_in, 
     IterFn iter = method == 2 ? enqueue_gpad : pick_iter(o.mem, o.nu_max);
     // each halving of lambda costs one update that does not count
     const int last = o.max_iter + (backtrack ? kBtMax + 1 : 0);
-    int k = 0, ndone = 0;
+    int k = 0, ndone = 0, ahead = 0;
+    // instances finished by the last check are skipped by the sweeps (the
+    // count may lag behind by check_every iterations and one; it only grows)
+    auto enqueue = [&]() -> hipError_t {
+        IterArgs it{x0, {ybuf[0], ybuf[1]}, k, method, f->ninst - ndone,
+                    div_window > 0 && k % div_window == 0, backtrack, o.trace, o.trace_iters};
+        ++k;
+        return iter(f, it, st);
+    };
     while (ndone < f->ninst && k <= last) {
-        // instances finished by the last check are skipped by the sweeps (the
-        // count may lag behind by check_every iterations; it only grows)
-        for (int c = 0; c < o.check_every && k <= last; ++c, ++k) {
-            IterArgs it{x0, {ybuf[0], ybuf[1]}, k, method, f->ninst - ndone,
-                        div_window > 0 && k % div_window == 0, backtrack, o.trace, o.trace_iters};
-            hipError_t e = iter(f, it, st);
-            if (e != hipSuccess) { set_error(std::string("solve: ") + hipGetErrorString(e)); return STOTREE_ERR_DEVICE; }
+        hipError_t e = hipSuccess;
+        for (int c = ahead; c < o.check_every && k <= last && e == hipSuccess; ++c) e = enqueue();
+        if (e == hipSuccess) e = hipMemcpyAsync(f->sws.ndone_host, w.ndone, sizeof(int), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipEventRecord(f->sws.polled, st);
+        // one more iteration goes in before the host waits for the count, so
+        // the device has work while it does (36 us a poll otherwise); if the
+        // count ends the solve, that iteration's kernels find every instance
+        // finished and return
+        ahead = 0;
+        if (e == hipSuccess && k <= last) {
+            e = enqueue();
+            ahead = 1;
         }
-        STOTREE_HIP(hipMemcpyAsync(&ndone, w.ndone, sizeof(int), hipMemcpyDeviceToHost, st));
-        STOTREE_HIP(hipStreamSynchronize(st));
+        if (e != hipSuccess) {
+            (void)hipStreamSynchronize(st);    // what is queued writes the caller's buffers
+            set_error(std::string("solve: ") + hipGetErrorString(e));
+            return STOTREE_ERR_DEVICE;
+        }
+        STOTREE_HIP(hipEventSynchronize(f->sws.polled));
+        ndone = *f->sws.ndone_host;
     }
     if (method != 2) {
         // last iterate of every instance into y_io (GPAD keeps it there)
