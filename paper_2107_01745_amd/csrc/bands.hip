@@ -204,7 +204,6 @@ __device__ __forceinline__ void band_bwd(const SweepArgs &a, const InstDesc &I, 
     int lev, k, i = 0, cnt = 0;
     // this group's node of the next chunk (the stage's last one past the end) and its loads
     auto fetch = [&]() {
-        s.next<true>(wave, lane, lev, k);
         if (lev < 0) return;
         cnt = s.cnt(lev);
         i = s.lo(lev) + (k + grp < cnt ? k + grp : cnt - 1);
@@ -234,9 +233,27 @@ __device__ __forceinline__ void band_bwd(const SweepArgs &a, const InstDesc &I, 
         }
         if (lev > 0) m.open(pM, (unsigned)i * (unsigned)(nx * ldM * 8) + cM, ldM, nx);
     };
+    // -R~^{-1} g of the node just done: only the forward pass needs it, so it is
+    // formed after the barrier, while the stage above is on its way, unless this
+    // wavefront has a chunk of that stage (4,095-node two-mode tree 54 -> 49 us a
+    // sweep)
+    int ki = 0;
+    bool kown = false;
+    auto store_k = [&]() {
+        double ra[NRHS][2];
+        rn.template run<NRHS>(v + nx, ldv, ra);
+        const unsigned ou = (unsigned)ki * nu + c0;
+#pragma unroll
+        for (int r = 0; r < NRHS; ++r)
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                if (c0 + e < nu && kown) (pk + r * a.kbuf_rs)[ou + e] = ra[r][e];
+    };
     s.task = 0;
+    s.next<true>(wave, lane, lev, k);
     fetch();
     for (int t = edge; t >= 0; --t) {
+        bool behind = false;                       // k and the next chunk's loads are still to do
         const double *pb = buf + ((t + 1) & 1) * half + (c0 < ldM ? c0 : 0);
         double *pw = buf + (t & 1) * half + c0;
         const int lo1 = t < edge ? s.lo(t + 1) : 0;
@@ -270,16 +287,16 @@ __device__ __forceinline__ void band_bwd(const SweepArgs &a, const InstDesc &I, 
                     *reinterpret_cast<double2 *>(v + r * ldv + c0) = make_double2(w[r][0], w[r][1]);
             wave_sync();
             if (t < edge) {
-                double ka[NRHS][2], ra[NRHS][2];
-                rn.template run<NRHS>(v + nx, ldv, ra);
+                double ka[NRHS][2];
                 kb.template run<NRHS>(v + nx, ldv, ka);
-                const unsigned ou = (unsigned)i * nu + c0, ox = (unsigned)i * nx + c0;
+                const unsigned ox = (unsigned)i * nx + c0;
                 const bool out = t == 0 && i > 0 && own;
+                ki = i;
+                kown = own;
 #pragma unroll
                 for (int r = 0; r < NRHS; ++r)
 #pragma unroll
                     for (int e = 0; e < 2; ++e) {
-                        if (c0 + e < nu && own) (pk + r * a.kbuf_rs)[ou + e] = ra[r][e];
                         if (c0 + e < nx) {
                             const double q = w[r][e] + ka[r][e];
                             v[r * ldv + c0 + e] = q;
@@ -295,11 +312,21 @@ __device__ __forceinline__ void band_bwd(const SweepArgs &a, const InstDesc &I, 
 #pragma unroll
                     for (int r = 0; r < NRHS; ++r)
                         *reinterpret_cast<double2 *>(pw + (j * NRHS + r) * ldM) = make_double2(pa[r][0], pa[r][1]);
-                wave_sync();     // the next chunk overwrites v
             }
+            s.next<true>(wave, lane, lev, k);
+            // (a chunk of the very next stage needs its loads now)
+            behind = lev < t - 1;
+            if (behind) break;
+            if (t < edge) store_k();
+            wave_sync();         // the next chunk overwrites v
             fetch();
         }
         if (t > 0) lds_barrier();
+        if (behind) {
+            if (t < edge) store_k();
+            wave_sync();
+            fetch();
+        }
     }
 }
 
@@ -327,7 +354,6 @@ __device__ __forceinline__ void band_fwd(const SweepArgs &a, const InstDesc &I, 
     int par = 0;
     int lev, k, i = 0, cnt = 0;
     auto fetch = [&]() {
-        s.next<false>(wave, lane, lev, k);
         if (lev < 0) return;
         cnt = s.cnt(lev);
         i = s.lo(lev) + (k + grp < cnt ? k + grp : cnt - 1);
@@ -358,6 +384,7 @@ __device__ __forceinline__ void band_fwd(const SweepArgs &a, const InstDesc &I, 
         }
     };
     s.task = 0;
+    s.next<false>(wave, lane, lev, k);
     fetch();
     for (int t = 0; t <= edge; ++t) {
         const int lo1 = t > 0 ? s.lo(t - 1) : 0;
@@ -404,6 +431,7 @@ __device__ __forceinline__ void band_fwd(const SweepArgs &a, const InstDesc &I, 
                             xu[r * ldM + nx + c0 + e] = u;
                         }
             }
+            s.next<false>(wave, lane, lev, k);
             fetch();
         }
         if (t < edge) lds_barrier();
