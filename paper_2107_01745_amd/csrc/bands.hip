@@ -514,23 +514,15 @@ std::vector<int> band_cuts(const InstDesc &I, const int *sp, const int *cp, int 
     return cut;
 }
 
-void free_bands(tree_factors *f)
-{
-    for (BandPlan &b : f->bands)
-        for (int c = 0; c < 2; ++c)
-            if (b.items[c]) (void)hipFree(b.items[c]);
-    f->bands.clear();
-    if (f->band_tabs) { (void)hipFree(f->band_tabs); f->band_tabs = nullptr; }
-}
-
 // Work lists of the bands; cuts[b] is instance b's cut list (empty: the
 // instance runs per stage).  cp: host child pointers.
-int build_bands(tree_factors *f, const std::vector<std::vector<int>> &cuts)
+void build_bands(tree_factors *f, const std::vector<std::vector<int>> &cuts, ListArena &arena)
 {
-    free_bands(f);
+    f->bands.clear();
+    f->band_tabs = nullptr;
     size_t nb = 0;
     for (const auto &c : cuts) nb = std::max(nb, c.size());
-    if (nb < 2) return STOTREE_OK;
+    if (nb < 2) return;
     std::vector<int> tabs;
     std::vector<std::vector<Item>> items((nb - 1) * 2);
     f->bands.resize(nb - 1);
@@ -563,17 +555,12 @@ int build_bands(tree_factors *f, const std::vector<std::vector<int>> &cuts)
             }
         }
     }
-    STOTREE_HIP(hipMalloc(&f->band_tabs, sizeof(int) * tabs.size()));
-    STOTREE_HIP(hipMemcpy(f->band_tabs, tabs.data(), sizeof(int) * tabs.size(), hipMemcpyHostToDevice));
+    f->band_tabs = arena.put(tabs);
     for (size_t k = 0; k + 1 < nb; ++k)
         for (int c = 0; c < 2; ++c) {
-            const std::vector<Item> &v = items[2 * k + c];
-            f->bands[k].count[c] = (int)v.size();
-            if (v.empty()) continue;
-            STOTREE_HIP(hipMalloc(&f->bands[k].items[c], sizeof(Item) * v.size()));
-            STOTREE_HIP(hipMemcpy(f->bands[k].items[c], v.data(), sizeof(Item) * v.size(), hipMemcpyHostToDevice));
+            f->bands[k].count[c] = (int)items[2 * k + c].size();
+            f->bands[k].items[c] = arena.put(items[2 * k + c]);
         }
-    return STOTREE_OK;
 }
 
 template <int NRHS>

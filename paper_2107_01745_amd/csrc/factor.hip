@@ -508,11 +508,18 @@ __global__ void __launch_bounds__(kFactorThreads) factor_stage_kernel(FactorArgs
         a.sig[I.sig + (long long)i * nu + rr] = a.hasr ? pi * a.r[Rw.r + (long long)i * nu + rr] : 0.0;
 }
 
+// x * 0 is 0 for a finite x and NaN otherwise: eight running sums of it need no
+// branch per entry and vectorise (a loop of isfinite tests took 1 ms per 28 MB,
+// a quarter of the factor step of the 2,794-node tree; this 0.45).
 bool all_finite(const double *a, size_t n)
 {
-    for (size_t k = 0; k < n; ++k)
-        if (!std::isfinite(a[k])) return false;
-    return true;
+    double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    size_t k = 0;
+    for (; k + 8 <= n; k += 8)
+        for (int u = 0; u < 8; ++u) s[u] += a[k + u] * 0.0;
+    for (; k < n; ++k) s[0] += a[k] * 0.0;
+    for (int u = 1; u < 8; ++u) s[0] += s[u];
+    return s[0] == 0.0;
 }
 
 // Device buffer freed at scope exit.
@@ -647,14 +654,38 @@ int trunk_waves(int n, int nrhs_max, int ldM, int cap)
     return nw;
 }
 
-void free_level(LevelPlan &lv)
+// The lists of a schedule, by their device pointers.
+template <typename F>
+void each_list(tree_factors *f, F fn)
 {
-    if (lv.items) (void)hipFree(lv.items);
-    if (lv.wide_items) (void)hipFree(lv.wide_items);
-    for (auto &g : lv.narrow)
-        if (g.items) (void)hipFree(g.items);
-    lv.items = lv.wide_items = nullptr;
-    lv.narrow.clear();
+    auto level = [&](LevelPlan &lv) {
+        fn(lv.items);
+        fn(lv.wide_items);
+        for (auto &g : lv.narrow) fn(g.items);
+    };
+    for (auto &cp : f->chains) fn(cp.items);
+    for (auto *v : {&f->levels, &f->panel_levels, &f->rest_levels})
+        for (auto &lv : *v) level(lv);
+    for (LevelPlan *lv : {&f->fused_bwd, &f->fused_fwd, &f->trunk_entry}) level(*lv);
+    fn(f->panel_chain_items);
+    for (auto &b : f->bands)
+        for (Item *&it : b.items) fn(it);
+    fn(f->band_tabs);
+}
+
+void clear_schedule(tree_factors *f)
+{
+    f->chains.clear();
+    f->levels.clear();
+    f->panel_levels.clear();
+    f->rest_levels.clear();
+    f->bands.clear();
+    f->fused_bwd = f->fused_fwd = f->trunk_entry = LevelPlan{};
+    f->panel_chain_items = nullptr;
+    f->npanel_chain_items = 0;
+    f->band_tabs = nullptr;
+    if (f->sched) (void)hipFree(f->sched);
+    f->sched = nullptr;
 }
 
 }  // namespace
@@ -671,16 +702,8 @@ void free_tree(tree_factors *f)
     if (f->d_inst_xu && f->d_inst_xu != f->d_inst) (void)hipFree(f->d_inst_xu);
     if (f->sws.ndone_host) (void)hipHostFree(f->sws.ndone_host);
     if (f->sws.polled) (void)hipEventDestroy(f->sws.polled);
-    for (auto &cp : f->chains)
-        if (cp.items) (void)hipFree(cp.items);
-    for (auto &lv : f->levels) free_level(lv);
-    for (auto &lv : f->panel_levels) free_level(lv);
-    for (auto &lv : f->rest_levels) free_level(lv);
-    free_level(f->fused_bwd);
-    free_level(f->fused_fwd);
-    free_bands(f);
-    for (void *p : {(void *)f->panel_chain_items, (void *)f->trunk_entry.items, (void *)f->trunk_cnt,
-                    (void *)f->Pcal})
+    clear_schedule(f);
+    for (void *p : {(void *)f->trunk_cnt, (void *)f->Pcal})
         if (p) (void)hipFree(p);
     delete f;
 }
@@ -713,11 +736,8 @@ constexpr int kBandChainStages = 3;
 // node) pairs of that stage.
 int build_schedule(tree_factors *f)
 {
-    for (auto &cp : f->chains)
-        if (cp.items) (void)hipFree(cp.items);
-    f->chains.clear();
-    for (auto &lv : f->levels) free_level(lv);
-    f->levels.clear();
+    clear_schedule(f);
+    ListArena arena;
     int max_sstar = 0, max_ldM = 0;
     // launch form 0: the stages above s* in bands, and a short chain part with them
     std::vector<std::vector<int>> cuts(f->ninst);
@@ -734,8 +754,7 @@ int build_schedule(tree_factors *f)
         }
         if (!all) cuts.assign(f->ninst, {});
     }
-    int rc = build_bands(f, cuts);
-    if (rc) return rc;
+    build_bands(f, cuts, arena);
     std::map<int, std::vector<std::pair<double, Item>>> by_G;
     std::map<int, int> ldq_G;
     for (int b = 0; b < f->ninst; ++b) {
@@ -751,9 +770,6 @@ int build_schedule(tree_factors *f)
             by_G[G].push_back({(double)(I.N - I.sstar) * I.nx * (I.nx + I.nu) * n, Item{b, c}});
         }
     }
-    if (f->panel_chain_items) { (void)hipFree(f->panel_chain_items); f->panel_chain_items = nullptr; }
-    for (auto &lv : f->panel_levels) free_level(lv);
-    f->panel_levels.clear();
     const int panel_inst = f->shared > 1 ? 1 : f->ninst;   // a shared handle's panels cover instance 0's nodes
     {
         std::vector<Item> all;
@@ -763,11 +779,7 @@ int build_schedule(tree_factors *f)
                 for (int c = 0; c < I.nchains; ++c) all.push_back({b, c});
         }
         f->npanel_chain_items = (int)all.size();
-        if (!all.empty()) {
-            STOTREE_HIP(hipMalloc(&f->panel_chain_items, sizeof(Item) * all.size()));
-            STOTREE_HIP(hipMemcpy(f->panel_chain_items, all.data(), sizeof(Item) * all.size(),
-                                  hipMemcpyHostToDevice));
-        }
+        f->panel_chain_items = arena.put(all);
     }
     for (auto &kv : by_G) {
         auto &v = kv.second;
@@ -780,9 +792,8 @@ int build_schedule(tree_factors *f)
         cp.ldq = ldq_G[kv.first];
         cp.CH = cp.ldq > 2 * cp.G ? 2 : 1;
         cp.count = (int)items.size();
-        STOTREE_HIP(hipMalloc(&cp.items, sizeof(Item) * items.size()));
+        cp.items = arena.put(items);
         f->chains.push_back(cp);
-        STOTREE_HIP(hipMemcpy(cp.items, items.data(), sizeof(Item) * items.size(), hipMemcpyHostToDevice));
     }
     for (int t = 0; t < max_sstar; ++t) {
         std::vector<Item> items;
@@ -796,9 +807,8 @@ int build_schedule(tree_factors *f)
         lv.t = t;
         lv.count = (int)items.size();
         lv.nw = trunk_waves(lv.count, 2, max_ldM, f->trunk_cap);
-        STOTREE_HIP(hipMalloc(&lv.items, sizeof(Item) * std::max<size_t>(1, items.size())));
+        lv.items = arena.put(items);
         f->levels.push_back(lv);
-        STOTREE_HIP(hipMemcpy(lv.items, items.data(), sizeof(Item) * items.size(), hipMemcpyHostToDevice));
         if (f->trunk_fused <= 2) {
             // the nodes of the instances that are not swept in bands; in mode 2
             // lane groups for the narrow ones, workgroups for the rest
@@ -822,20 +832,15 @@ int build_schedule(tree_factors *f)
             }
             L.wide_count = (int)wide.size();
             L.wide_nw = trunk_waves(L.wide_count, 2, wide_ldM, f->trunk_cap);
-            if (!wide.empty()) {
-                STOTREE_HIP(hipMalloc(&L.wide_items, sizeof(Item) * wide.size()));
-                STOTREE_HIP(hipMemcpy(L.wide_items, wide.data(), sizeof(Item) * wide.size(), hipMemcpyHostToDevice));
-            }
+            L.wide_items = arena.put(wide);
             for (auto &kv : groups) {
                 ChainPlan g{};
                 g.G = kv.first;
                 g.CH = 1;
                 g.ldq = gldq[kv.first];
                 g.count = (int)kv.second.size();
-                STOTREE_HIP(hipMalloc(&g.items, sizeof(Item) * kv.second.size()));
+                g.items = arena.put(kv.second);
                 L.narrow.push_back(g);
-                STOTREE_HIP(hipMemcpy(g.items, kv.second.data(), sizeof(Item) * kv.second.size(),
-                                      hipMemcpyHostToDevice));
             }
         }
         if (panel_inst < f->ninst) {
@@ -844,20 +849,13 @@ int build_schedule(tree_factors *f)
             pl.t = t;
             pl.nw = lv.nw;
             pl.count = t < I.sstar ? f->sp_pool[I.sp + t + 1] - f->sp_pool[I.sp + t] : 0;
-            STOTREE_HIP(hipMalloc(&pl.items, sizeof(Item) * std::max(1, pl.count)));
+            pl.items = arena.put(std::vector<Item>(items.begin(), items.begin() + pl.count));
             f->panel_levels.push_back(pl);
-            STOTREE_HIP(hipMemcpy(pl.items, items.data(), sizeof(Item) * pl.count, hipMemcpyHostToDevice));
         }
     }
     // trunk modes 3 and 4: each instance's first stages with at most
     // fuse_limit nodes run in one launch per direction (deepest stage first
     // backward, root first forward); the other stages above s* one launch each
-    free_level(f->fused_bwd);
-    free_level(f->fused_fwd);
-    f->fused_bwd = LevelPlan{};
-    f->fused_fwd = LevelPlan{};
-    for (auto &lv : f->rest_levels) free_level(lv);
-    f->rest_levels.clear();
     if (f->trunk_fused >= 3) {
         const int lim = fuse_limit(f->trunk_fused);
         std::vector<int> depth(f->ninst, 0);
@@ -890,9 +888,7 @@ int build_schedule(tree_factors *f)
             lv.t = -1;
             lv.count = (int)v.size();
             lv.nw = trunk_waves(widest, 2, max_ldM, f->trunk_cap);
-            if (v.empty()) continue;
-            STOTREE_HIP(hipMalloc(&lv.items, sizeof(Item) * v.size()));
-            STOTREE_HIP(hipMemcpy(lv.items, v.data(), sizeof(Item) * v.size(), hipMemcpyHostToDevice));
+            lv.items = arena.put(v);
         }
         for (int t = 0; t < max_sstar; ++t) {
             std::vector<Item> items;
@@ -907,14 +903,11 @@ int build_schedule(tree_factors *f)
             lv.t = t;
             lv.count = (int)items.size();
             lv.nw = trunk_waves(lv.count, 2, max_ldM, f->trunk_cap);
-            STOTREE_HIP(hipMalloc(&lv.items, sizeof(Item) * items.size()));
+            lv.items = arena.put(items);
             f->rest_levels.push_back(lv);
-            STOTREE_HIP(hipMemcpy(lv.items, items.data(), sizeof(Item) * items.size(), hipMemcpyHostToDevice));
         }
     }
     // one-launch backward trunk: its entry nodes and the per-node counters
-    if (f->trunk_entry.items) { (void)hipFree(f->trunk_entry.items); f->trunk_entry.items = nullptr; }
-    f->trunk_entry.count = 0;
     {
         std::vector<Item> entry;
         for (int b = 0; b < f->ninst; ++b) {
@@ -926,14 +919,24 @@ int build_schedule(tree_factors *f)
         f->trunk_entry.t = -1;
         f->trunk_entry.count = (int)entry.size();
         f->trunk_entry.nw = trunk_waves(f->trunk_entry.count, 2, max_ldM, f->trunk_cap);
-        if (!entry.empty()) {
-            STOTREE_HIP(hipMalloc(&f->trunk_entry.items, sizeof(Item) * entry.size()));
-            STOTREE_HIP(hipMemcpy(f->trunk_entry.items, entry.data(), sizeof(Item) * entry.size(),
-                                  hipMemcpyHostToDevice));
-            if (!f->trunk_cnt) STOTREE_HIP(hipMalloc(&f->trunk_cnt, sizeof(int) * (size_t)(f->V_tot + 1)));
-            // counters, flags and the fused launches' error word start at zero
-            STOTREE_HIP(hipMemset(f->trunk_cnt, 0, sizeof(int) * (size_t)(f->V_tot + 1)));
-        }
+        f->trunk_entry.items = arena.put(entry);
+    }
+    // the lists go to the device in one piece
+    hipError_t e = hipSuccess;
+    if (!arena.host.empty()) {
+        e = hipMalloc(&f->sched, arena.host.size());
+        if (e != hipSuccess) f->sched = nullptr;
+        else e = hipMemcpy(f->sched, arena.host.data(), arena.host.size(), hipMemcpyHostToDevice);
+    }
+    each_list(f, [&](auto *&p) { ListArena::settle(p, f->sched); });
+    if (e == hipSuccess && f->trunk_entry.count > 0) {
+        // counters, flags and the fused launches' error word start at zero
+        if (!f->trunk_cnt) e = hipMalloc(&f->trunk_cnt, sizeof(int) * (size_t)(f->V_tot + 1));
+        if (e == hipSuccess) e = hipMemset(f->trunk_cnt, 0, sizeof(int) * (size_t)(f->V_tot + 1));
+    }
+    if (e != hipSuccess) {
+        clear_schedule(f);     // no list may point nowhere
+        STOTREE_HIP(e);
     }
     return STOTREE_OK;
 }
@@ -1203,9 +1206,47 @@ int factor_forest(int count, const tree_desc *trees, const problem_data *datas, 
         STOTREE_HIP(hipMemcpy(f->hi, hi.data(), sizeof(double) * oy, hipMemcpyHostToDevice));
     }
     // raw inputs: concatenated pools (a single instance is uploaded in place)
-    DevBuf bA, bB, bc, bQ, bR, bS, bq, br, bP, bp, bprob, bPcal, bscr, berr, braw, bitems;
-    auto upload = [&](DevBuf &buf, long long total, auto get, auto len) -> int {
-        STOTREE_HIP(hipMalloc(&buf.p, sizeof(double) * (total ? total : 1)));
+    // (raw inputs, work lists and scratch in one temporary allocation)
+    struct Part { void *p = nullptr; };
+    Part bA, bB, bc, bQ, bR, bS, bq, br, bP, bp, bprob, bscr, berr, braw, bitems;
+    DevBuf btmp, bPcal;
+    std::vector<std::vector<Item>> level_items;
+    int maxw = 1, max_depth = 0;
+    for (int b = 0; b < count; ++b) max_depth = std::max(max_depth, f->inst[b].N);
+    level_items.resize(max_depth);
+    size_t nitems = 0;
+    for (int b = 0; b < count; ++b) {
+        const InstDesc &I = f->inst[b];
+        const int *sp = f->sp_pool.data() + I.sp;
+        for (int t = 0; t < I.N; ++t)
+            for (int i = sp[t]; i < sp[t + 1]; ++i) level_items[t].push_back({b, i});
+    }
+    for (auto &li : level_items) {
+        maxw = std::max<int>(maxw, (int)li.size());
+        nitems += li.size();
+    }
+    {
+        size_t bytes = 0;
+        std::vector<std::pair<Part *, size_t>> parts;
+        auto want = [&](Part &q, size_t n) {
+            parts.push_back({&q, bytes});
+            bytes += (n + 255) / 256 * 256;
+        };
+        want(bA, 8 * ro.A); want(bB, 8 * ro.B); want(bc, 8 * ro.c); want(bQ, 8 * ro.Q); want(bR, 8 * ro.R);
+        if (anyS) want(bS, 8 * ro.S);
+        if (anyq) want(bq, 8 * ro.q);
+        if (anyr) want(br, 8 * ro.r);
+        want(bP, 8 * ro.P);
+        if (anyp) want(bp, 8 * ro.p);
+        want(bprob, 8 * ro.prob);
+        want(bscr, sizeof(double) * (size_t)maxw * max_slot);
+        want(berr, sizeof(int));
+        want(braw, sizeof(RawDesc) * count);
+        want(bitems, sizeof(Item) * nitems);
+        STOTREE_HIP(hipMalloc(&btmp.p, std::max<size_t>(bytes, 256)));
+        for (auto &q : parts) q.first->p = (char *)btmp.p + q.second;
+    }
+    auto upload = [&](Part &buf, long long, auto get, auto len) -> int {
         long long o = 0;
         for (int b = 0; b < count; ++b) {
             const double *h = get(b);
@@ -1230,22 +1271,7 @@ int factor_forest(int count, const tree_desc *trees, const problem_data *datas, 
         (rc = upload(bprob, ro.prob, [&](int b) { return trees[b].prob; }, NODES((long long)I.V))))
         return rc;
 #undef NODES
-    // scratch for the widest stage
-    int maxw = 1;
-    int max_depth = 0;
-    for (int b = 0; b < count; ++b) max_depth = std::max(max_depth, f->inst[b].N);
-    std::vector<std::vector<Item>> level_items(max_depth);
-    for (int b = 0; b < count; ++b) {
-        const InstDesc &I = f->inst[b];
-        const int *sp = f->sp_pool.data() + I.sp;
-        for (int t = 0; t < I.N; ++t)
-            for (int i = sp[t]; i < sp[t + 1]; ++i) level_items[t].push_back({b, i});
-    }
-    for (auto &li : level_items) maxw = std::max<int>(maxw, (int)li.size());
     STOTREE_HIP(hipMalloc(&bPcal.p, sizeof(double) * (size_t)std::max(1LL, ro.Pcal)));
-    STOTREE_HIP(hipMalloc(&bscr.p, sizeof(double) * (size_t)maxw * max_slot));
-    STOTREE_HIP(hipMalloc(&berr.p, sizeof(int)));
-    STOTREE_HIP(hipMalloc(&braw.p, sizeof(RawDesc) * count));
     std::vector<Item> all_items;
     std::vector<size_t> level_off(max_depth + 1, 0);
     for (int t = 0; t < max_depth; ++t) {
@@ -1253,7 +1279,6 @@ int factor_forest(int count, const tree_desc *trees, const problem_data *datas, 
         all_items.insert(all_items.end(), level_items[t].begin(), level_items[t].end());
     }
     level_off[max_depth] = all_items.size();
-    STOTREE_HIP(hipMalloc(&bitems.p, sizeof(Item) * std::max<size_t>(1, all_items.size())));
     STOTREE_HIP(hipMemcpy(bitems.p, all_items.data(), sizeof(Item) * all_items.size(), hipMemcpyHostToDevice));
     STOTREE_HIP(hipMemcpy(braw.p, raw.data(), sizeof(RawDesc) * count, hipMemcpyHostToDevice));
     STOTREE_HIP(hipMemset(berr.p, 0, sizeof(int)));

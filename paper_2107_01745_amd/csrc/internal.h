@@ -11,6 +11,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <cstring>
 #include <map>
 #include <string>
 #include <vector>
@@ -148,7 +149,8 @@ struct tree_factors {
     double *Pcal = nullptr;                 // value-function Hessians [V][nx][nx] (kept only on request)
     long long m_tot = 0, n_tot = 0, x_tot = 0, u_tot = 0, nx_tot = 0, V_tot = 0;
     int max_width = 0;                      // max nx+nu over instances
-    // schedule of a sweep
+    // schedule of a sweep; its lists all live in one device allocation
+    char *sched = nullptr;
     std::vector<stotree::ChainPlan> chains;  // stages s*..N, one plan per lane-group width
     std::vector<stotree::LevelPlan> levels;  // stages 0..max(s*)-1
     std::vector<stotree::BandPlan> bands;   // narrow instances' stages, first band at the root
@@ -185,6 +187,29 @@ struct tree_factors {
 namespace stotree {
 
 void set_error(const std::string &msg);
+
+// The device lists of a schedule while they are built: put copies a list to
+// the host side of one allocation and returns a stand-in for its device
+// pointer (its offset plus one), which settle turns into the pointer once the
+// allocation exists.  (A list at a time took an allocation and an upload each,
+// 36 us a list, 15 to 40 of them per handle.)
+struct ListArena {
+    std::vector<char> host;
+    template <typename T>
+    T *put(const std::vector<T> &v)
+    {
+        if (v.empty()) return nullptr;
+        const size_t o = (host.size() + 63) / 64 * 64, n = sizeof(T) * v.size();
+        host.resize(o + n);
+        std::memcpy(host.data() + o, v.data(), n);
+        return reinterpret_cast<T *>(o + 1);
+    }
+    template <typename T>
+    static void settle(T *&p, char *base)
+    {
+        if (p) p = base ? reinterpret_cast<T *>(base + (reinterpret_cast<size_t>(p) - 1)) : nullptr;
+    }
+};
 
 // factor.hip
 int factor_forest(int count, const tree_desc *t, const problem_data *d, int precondition,
@@ -227,8 +252,8 @@ int dual_grad_noalloc_impl(const tree_factors *f, const double *x0, const double
 
 // bands.hip
 std::vector<int> band_cuts(const InstDesc &I, const int *sp, const int *cp, int last);
-int build_bands(tree_factors *f, const std::vector<std::vector<int>> &cuts);
-void free_bands(tree_factors *f);
+struct ListArena;
+void build_bands(tree_factors *f, const std::vector<std::vector<int>> &cuts, ListArena &arena);
 // pass 0: backward, 1: forward, 2: both (band 0)
 void launch_band(const tree_factors *f, const SweepArgs &a, int nrhs, int band, int pass, hipStream_t st);
 
