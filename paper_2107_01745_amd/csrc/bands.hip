@@ -21,10 +21,9 @@
 // What bounds it: the chain of dependent steps, one per stage, and the
 // instructions in it (a wavefront has its SIMD to itself).  What a wavefront's
 // next nodes need (their matrices' first rows, their own vector entries) is
-// requested before the barrier in front of them.  A stage takes about 1.2 us in
-// each direction (nx=4, nu=2, 15 of them in 16 us; 1.7 us with barriers that
-// wait for the loads in flight and per-row selects), where a launch per stage
-// took 6.
+// requested before the barrier in front of them.  A stage takes about 1.1 us in
+// each direction (nx=4, nu=2: 12 steps in 16 us, 24 with barriers that wait for
+// the loads in flight and a select per row), where a launch per stage took 6.
 #include <algorithm>
 
 #include "sweep_common.h"
@@ -489,8 +488,10 @@ std::vector<int> band_cuts(const InstDesc &I, const int *sp, const int *cp, int 
 {
     std::vector<int> cut;
     if (I.ldM > kBandWidth || last < 1) return cut;
-    // node offsets of a matrix pool are 32-bit byte offsets
-    if (8LL * I.V * std::max<long long>((long long)I.nx * I.ldM, (long long)(I.nx + I.nu) * I.ldx) >= 1LL << 32) return cut;
+    // a node's offset in each matrix pool is a 32-bit byte offset
+    const long long per = std::max({(long long)I.nx * I.ldM, (long long)(I.nx + I.nu) * I.ldx, (long long)I.nu * I.ldu,
+                                    (long long)I.nu * I.ldx, (long long)I.nx * I.ldu});
+    if (8LL * I.V * per >= 1LL << 32) return cut;
     const int most = band_nodes(I);
     cut.push_back(0);
     for (int t = 0; t < last;) {
