@@ -36,6 +36,7 @@
 // place of the hard bound, Sec. II-B), and the constraint map z = [F G] (x, u)
 // around the sweeps (cmap.hip).
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -420,7 +421,10 @@ __global__ void __launch_bounds__(kVB) combine_kernel(VecArgs a)
 }
 
 // The row prox of a line search, where one row is tried at many points: the
-// quotients that do not depend on the point, formed once.
+// quotients that do not depend on the point, formed once.  Where w / (2 d)
+// overflows (a Huber threshold near the smallest doubles), h is the largest
+// double: the shrunk distance there is zero or some 1e-308 of the distance, and
+// infinity times it would be NaN.
 struct RowTrial {
     double lo, hi, w, d, wl, q, h;   // wl = w / lambda, q = 1 + wl / d, h = w / (2 d)
 };
@@ -431,7 +435,7 @@ __device__ __forceinline__ RowTrial row_trial(const RowG &g, double lam)
         t.wl = g.w / lam;
         if (g.d > 0.0) {
             t.q = 1.0 + t.wl / g.d;
-            t.h = g.w / (2.0 * g.d);
+            t.h = fmin(g.w / (2.0 * g.d), DBL_MAX);
         }
     }
     return t;
