@@ -294,8 +294,9 @@ int dual_grad_noalloc(const tree_factors *f, const double *x0, const double *y, 
  * knobs[1] changes no result bit; knobs[0], knobs[2], knobs[3] and knobs[4]
  * change the order of some per-node sums (equal to rounding).
  * sweep_schedule rebuilds the work lists (synchronous; ERR_ARG for values
- * outside these sets, ERR_OOM, ERR_DEVICE); sweep_schedule_get reads them.
- * A schedule change invalidates the handle's sweep graphs.
+ * outside these sets, ERR_OOM, ERR_DEVICE; on an error the handle keeps the
+ * schedule it had); sweep_schedule_get reads them.  A schedule change
+ * invalidates the handle's sweep graphs.
  */
 int sweep_schedule(tree_factors *f, const int32_t *knobs);
 int sweep_schedule_get(const tree_factors *f, int32_t *knobs);
@@ -312,7 +313,7 @@ int sweep_schedule_get(const tree_factors *f, int32_t *knobs);
  * elsewhere knobs[4] is left as it is.  HOST knobs_out[5] and ms_out
  * (milliseconds per sweep of the kept schedule, all copies) may be NULL.
  * Allocates and frees its own scratch; synchronous.  Errors: ERR_ARG,
- * ERR_OOM, ERR_DEVICE.
+ * ERR_OOM, ERR_DEVICE (the schedule is then the one before the call).
  */
 int sweep_autotune(tree_factors *f, int nrhs, int reps, int32_t *knobs_out, double *ms_out,
                    void *hip_stream);

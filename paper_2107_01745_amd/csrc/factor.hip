@@ -656,7 +656,7 @@ int trunk_waves(int n, int nrhs_max, int ldM, int cap)
 
 // The lists of a schedule, by their device pointers.
 template <typename F>
-void each_list(tree_factors *f, F fn)
+void each_list(Schedule *f, F fn)
 {
     auto level = [&](LevelPlan &lv) {
         fn(lv.items);
@@ -673,21 +673,6 @@ void each_list(tree_factors *f, F fn)
     fn(f->band_tabs);
 }
 
-void clear_schedule(tree_factors *f)
-{
-    f->chains.clear();
-    f->levels.clear();
-    f->panel_levels.clear();
-    f->rest_levels.clear();
-    f->bands.clear();
-    f->fused_bwd = f->fused_fwd = f->trunk_entry = LevelPlan{};
-    f->panel_chain_items = nullptr;
-    f->npanel_chain_items = 0;
-    f->band_tabs = nullptr;
-    if (f->sched) (void)hipFree(f->sched);
-    f->sched = nullptr;
-}
-
 }  // namespace
 
 void free_tree(tree_factors *f)
@@ -702,8 +687,7 @@ void free_tree(tree_factors *f)
     if (f->d_inst_xu && f->d_inst_xu != f->d_inst) (void)hipFree(f->d_inst_xu);
     if (f->sws.ndone_host) (void)hipHostFree(f->sws.ndone_host);
     if (f->sws.polled) (void)hipEventDestroy(f->sws.polled);
-    clear_schedule(f);
-    for (void *p : {(void *)f->trunk_cnt, (void *)f->Pcal})
+    for (void *p : {(void *)f->trunk_cnt, (void *)f->Pcal, (void *)f->sched})
         if (p) (void)hipFree(p);
     delete f;
 }
@@ -733,10 +717,11 @@ constexpr int kBandChainStages = 3;
 // Work lists of a sweep: the chains, one plan per lane-group width (each item
 // a wavefront's worth of consecutive chains of one instance; the costliest
 // first when chain_order is set) and, per stage above s*, all (instance,
-// node) pairs of that stage.
+// node) pairs of that stage.  On an error the handle keeps the lists it had.
 int build_schedule(tree_factors *f)
 {
-    clear_schedule(f);
+    Schedule old = std::move(static_cast<Schedule &>(*f));
+    static_cast<Schedule &>(*f) = Schedule{};
     ListArena arena;
     int max_sstar = 0, max_ldM = 0;
     // launch form 0: the stages above s* in bands, and a short chain part with them
@@ -935,9 +920,11 @@ int build_schedule(tree_factors *f)
         if (e == hipSuccess) e = hipMemset(f->trunk_cnt, 0, sizeof(int) * (size_t)(f->V_tot + 1));
     }
     if (e != hipSuccess) {
-        clear_schedule(f);     // no list may point nowhere
+        if (f->sched) (void)hipFree(f->sched);
+        static_cast<Schedule &>(*f) = std::move(old);
         STOTREE_HIP(e);
     }
+    if (old.sched) (void)hipFree(old.sched);
     return STOTREE_OK;
 }
 

@@ -105,6 +105,22 @@ struct BandPlan {
     Item *items[2] = {nullptr, nullptr};   // device: (instance, offset of the subtree's table)
 };
 
+// The work lists of a sweep; they all live in one device allocation.  A rebuild
+// keeps the old ones until the new ones are on the device (build_schedule).
+struct Schedule {
+    char *sched = nullptr;
+    std::vector<ChainPlan> chains;   // stages s*..N, one plan per lane-group width
+    std::vector<LevelPlan> levels;   // stages 0..max(s*)-1
+    std::vector<BandPlan> bands;     // narrow instances' stages, first band at the root
+    int *band_tabs = nullptr;        // device: the subtrees' tables
+    Item *panel_chain_items = nullptr;     // (instance, chain) pairs of the panel sweeps
+    int npanel_chain_items = 0;
+    std::vector<LevelPlan> panel_levels;   // shared handles: instance 0's trunk nodes
+    LevelPlan trunk_entry{};         // nodes of stage s*-1 of every instance
+    LevelPlan fused_bwd{}, fused_fwd{};    // trunk modes 3, 4: the first stages' nodes
+    std::vector<LevelPlan> rest_levels;    // trunk modes 3, 4: the other stages above s*
+};
+
 // Solver workspace kept in the handle (allocated at the first solve).
 struct SolverWS {
     int mem = 0;
@@ -128,7 +144,7 @@ struct SolverWS {
 
 }  // namespace stotree
 
-struct tree_factors {
+struct tree_factors : stotree::Schedule {
     int ninst = 0, precondition = 0;
     std::vector<stotree::InstDesc> inst;    // host copy
     stotree::InstDesc *d_inst = nullptr;
@@ -149,18 +165,9 @@ struct tree_factors {
     double *Pcal = nullptr;                 // value-function Hessians [V][nx][nx] (kept only on request)
     long long m_tot = 0, n_tot = 0, x_tot = 0, u_tot = 0, nx_tot = 0, V_tot = 0;
     int max_width = 0;                      // max nx+nu over instances
-    // schedule of a sweep; its lists all live in one device allocation
-    char *sched = nullptr;
-    std::vector<stotree::ChainPlan> chains;  // stages s*..N, one plan per lane-group width
-    std::vector<stotree::LevelPlan> levels;  // stages 0..max(s*)-1
-    std::vector<stotree::BandPlan> bands;   // narrow instances' stages, first band at the root
-    int *band_tabs = nullptr;               // device: the subtrees' tables
-    stotree::Item *panel_chain_items = nullptr;  // (instance, chain) pairs of the panel sweeps
-    int npanel_chain_items = 0;
     // shared > 1: the instances are copies of instance 0 (same tree, factors
     // and boxes; own x0 and vectors), and panel sweeps run across instances
     int shared = 1;
-    std::vector<stotree::LevelPlan> panel_levels;  // shared handles: instance 0's trunk nodes
     // tuning knobs (sweep_schedule / sweep_autotune)
     int trunk_cap = 16;                     // cap on wavefronts per node above s*
     int chain_order = 1;                    // 1: longest chains first, 0: instance order
@@ -170,11 +177,8 @@ struct tree_factors {
                                             // the first stages (at most kFuseNodes[mode] nodes each)
                                             // in one launch per direction, the rest per stage
     int panel_min = 16;                     // shared handles: fewest unfinished copies swept as panels
-    stotree::LevelPlan trunk_entry{};       // nodes of stage s*-1 of every instance
     int *trunk_cnt = nullptr;               // per node (node0-indexed): children finished / parent
                                             // done; [V_tot]: error word of the fused launches
-    stotree::LevelPlan fused_bwd{}, fused_fwd{};  // trunk modes 3, 4: the first stages' nodes
-    std::vector<stotree::LevelPlan> rest_levels;  // trunk modes 3, 4: the other stages above s*
     long long schedule_epoch = 0;           // bumped whenever the work lists are rebuilt
     // sweep workspace (grows with nrhs)
     double *qhat = nullptr, *kbuf = nullptr;

@@ -66,13 +66,19 @@ int set_schedule(tree_factors *f, const int32_t *knobs)
     }
     // the old work lists may still be read by queued sweeps
     STOTREE_HIP(hipDeviceSynchronize());
-    f->group_min = knobs[0];
-    f->chain_order = knobs[1];
-    f->trunk_cap = knobs[2];
-    f->trunk_fused = knobs[3];
-    f->panel_min = knobs[4];
-    ++f->schedule_epoch;
-    return build_schedule(f);
+    auto set = [f](const int32_t *k) {
+        f->group_min = k[0];
+        f->chain_order = k[1];
+        f->trunk_cap = k[2];
+        f->trunk_fused = k[3];
+        f->panel_min = k[4];
+    };
+    const int32_t was[kKnobs] = {f->group_min, f->chain_order, f->trunk_cap, f->trunk_fused, f->panel_min};
+    set(knobs);
+    const int rc = build_schedule(f);
+    if (rc) set(was);                // the old lists stand, and with them the old knobs and graphs
+    else ++f->schedule_epoch;
+    return rc;
 }
 
 int autotune(tree_factors *f, int nrhs, int reps, int32_t *knobs_out, double *ms_out, hipStream_t st)
@@ -114,7 +120,8 @@ int autotune(tree_factors *f, int nrhs, int reps, int32_t *knobs_out, double *ms
         *ms = t / reps;
         return STOTREE_OK;
     };
-    int32_t best[kKnobs] = {f->group_min, f->chain_order, f->trunk_cap, f->trunk_fused, f->panel_min};
+    const int32_t was[kKnobs] = {f->group_min, f->chain_order, f->trunk_cap, f->trunk_fused, f->panel_min};
+    int32_t best[kKnobs] = {was[0], was[1], was[2], was[3], was[4]};
     const bool shared = shared_panels(f);
     if (shared) best[4] = kPanelMinMax;    // lane-group route while its knobs are tuned
     double best_ms = 0.0;
@@ -149,8 +156,14 @@ int autotune(tree_factors *f, int nrhs, int reps, int32_t *knobs_out, double *ms
         }
     }
     timing_enable(timing_was ? 1 : 0);
-    if (rc) return rc;
-    if ((rc = set_schedule(f, best))) return rc;
+    if (!rc) rc = set_schedule(f, best);
+    if (rc) {
+        // not a candidate's schedule, if it can be had
+        const std::string why = stotree_last_error();
+        (void)set_schedule(f, was);
+        set_error(why);
+        return rc;
+    }
     if (knobs_out) for (int k = 0; k < kKnobs; ++k) knobs_out[k] = best[k];
     if (ms_out) *ms_out = best_ms;
     return STOTREE_OK;

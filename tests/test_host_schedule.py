@@ -1,0 +1,44 @@
+"""Schedules of a handle, host side (no GPU: kernel launches are logged and not run)."""
+import hostsim
+
+
+def test_failed_rebuild_keeps_the_schedule():
+    """sweep_schedule and sweep_autotune that run out of memory leave the lists, the knobs and the
+    recorded graphs of the handle as they were: the next sweep launches what it launched before."""
+    hostsim.run("""
+        for prob in (problem([2, 2, 1, 1, 1, 1, 1], 4, 2), problem([3, 3, 1, 1], 40, 20)):
+            tf = factor(prob)
+            rc, before = sweep(tf)
+            assert rc == 0 and before
+            knobs = st.sweep_schedule_get(tf)
+            for at in range(3):
+                fake.fake_fail_mallocs_from(at)
+                try:
+                    st.sweep_schedule(tf, (16, 0, 4, 3, 5))
+                    ok = True
+                except st.StotreeError as e:
+                    assert e.code == -8, e
+                    ok = False
+                fake.fake_fail_mallocs_from(-1)
+                if ok:
+                    break
+                assert st.sweep_schedule_get(tf) == knobs
+                calls()
+                assert sweep(tf) == (0, before)
+            assert at > 0                       # at least one failure was seen
+            st.sweep_schedule(tf, knobs)
+            # the autotuner: its scratch, then a candidate's lists
+            for at in (0, 3, 6, 12):
+                fake.fake_fail_mallocs_from(at)
+                try:
+                    st.sweep_autotune(tf, stream=0)
+                    assert False
+                except st.StotreeError as e:
+                    assert e.code == -8, e
+                fake.fake_fail_mallocs_from(-1)
+                assert st.sweep_schedule_get(tf)[4] == knobs[4]
+                calls()
+                rc, now = sweep(tf)
+                assert rc == 0 and now
+            tf.free()
+    """)
