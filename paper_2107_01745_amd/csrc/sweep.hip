@@ -1705,9 +1705,27 @@ static void launch_chains(bool backward, const SweepArgs &a, const tree_factors 
     }
 }
 
+// Whether a sweep writes where it reads its duals.  Every launch order but the
+// first band's (backward and forward pass of an instance in one launch) has
+// read all duals before the first output, so a caller may sweep in place.
+static bool in_place(const tree_factors *f, const SweepArgs &a, int nrhs)
+{
+    auto meet = [](const double *p, long long n, const double *q, long long m) { return p < q + m && q < p + n; };
+    for (int k = 0; k < nrhs; ++k)
+        for (int j = 0; j < nrhs; ++j) {
+            const double *y = a.y + k * a.y_rs;
+            if (meet(y, f->mxu_tot, a.xo + j * a.xo_rs, a.dual_out ? f->mxu_tot : f->x_tot)) return true;
+            if (!a.dual_out && meet(y, f->mxu_tot, a.uo + j * a.uo_rs, f->u_tot)) return true;
+        }
+    return false;
+}
+
 template <int NRHS, int CH>
 static hipError_t sweep_impl(const tree_factors *f, SweepArgs a, hipStream_t st)
 {
+    // one instance's results must not overwrite another's duals (those of its own
+    // bands have been read when the first band writes)
+    const bool fwd_apart = !f->bands.empty() && f->ninst > 1 && in_place(f, a, NRHS);
     int ldM = 2, qs = 2, ldu = 2;
     for (const InstDesc &I : f->inst) {
         ldM = std::max(ldM, I.ldM);
@@ -1730,7 +1748,7 @@ static hipError_t sweep_impl(const tree_factors *f, SweepArgs a, hipStream_t st)
         } else {
             for (int k = (int)f->levels.size() - 1; k >= 0; --k)
                 launch_level<NRHS, CH>(true, a, f, f->levels[k], ldM, qs, ldu, st);
-            for (int b = (int)f->bands.size() - 1; b >= 0; --b) launch_band(f, a, NRHS, b, b == 0 ? 2 : 0, st);
+            for (int b = (int)f->bands.size() - 1; b >= 0; --b) launch_band(f, a, NRHS, b, b == 0 && !fwd_apart ? 2 : 0, st);
         }
     }
     if (!f->levels.empty() || !f->bands.empty()) {
@@ -1742,7 +1760,7 @@ static hipError_t sweep_impl(const tree_factors *f, SweepArgs a, hipStream_t st)
         } else {
             for (size_t k = 0; k < f->levels.size(); ++k)
                 launch_level<NRHS, CH>(false, a, f, f->levels[k], ldM, qs, ldu, st);
-            for (size_t b = 1; b < f->bands.size(); ++b) launch_band(f, a, NRHS, (int)b, 1, st);
+            for (size_t b = fwd_apart ? 0 : 1; b < f->bands.size(); ++b) launch_band(f, a, NRHS, (int)b, 1, st);
         }
     }
     if (!f->chains.empty()) {

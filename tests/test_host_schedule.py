@@ -42,3 +42,21 @@ def test_failed_rebuild_keeps_the_schedule():
                 assert rc == 0 and now
             tf.free()
     """)
+
+
+def test_sweep_in_place_on_a_batch():
+    """x or u in the memory of y: on a batch swept in bands no instance's results may be written while
+    another's duals are still to be read, so no launch does both directions; one tree alone may."""
+    hostsim.run("""
+        prob = problem([2, 2, 2], 4, 2)
+        both = lambda names: any("ELi2EE" in n for n in names if n.startswith("band_kernel"))
+        for tf, apart in ((factor(prob), False), (factor(prob, prob, prob), True)):
+            for nrhs in (1, 2):
+                y = buf(nrhs * tf.m)
+                for kw in (dict(x=y), dict(u=y), dict(x=y + 8 * (nrhs * tf.m - 1))):
+                    rc, names = sweep(tf, nrhs, y=y, **kw)
+                    assert rc == 0 and names and all(n.startswith("band_kernel") for n in names), names
+                    assert both(names) != apart, (names, nrhs)
+                assert both(sweep(tf, nrhs)[1])
+            tf.free()
+    """)
