@@ -271,10 +271,12 @@ int dual_grad_noalloc(const tree_factors *f, const double *x0, const double *y, 
  *   knobs[2] cap on the wavefronts sharing one node above s*: 1, 2, 4, 8 or
  *            16 (default 16);
  *   knobs[3] stages above s*: 0 (default) one launch per stage, a workgroup
- *            per node, or, on handles of few narrow trees (every nx + nu <= 32),
- *            bands of stages, a workgroup walking one subtree of a band per
- *            launch (with short chain parts too); 1 the backward stages in one launch in which each
- *            node is taken up by the workgroup that finishes its last child;
+ *            per node, or, on handles of few narrow trees (nx + nu <= 32 in
+ *            every instance with stages above s*), bands of stages, a
+ *            workgroup walking one subtree of a band per launch (with short
+ *            chain parts too); 1 the backward stages in one launch in which
+ *            each node is taken up by the workgroup that finishes its last
+ *            child;
  *            2 one launch per stage, the nodes of instances with nx + nu <= 64
  *            walked by lane groups as the chains are; 3 (4) each instance's
  *            first stages of at most 64 (256) nodes in one launch per

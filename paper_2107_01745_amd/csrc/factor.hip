@@ -699,20 +699,38 @@ int chain_group(int ldM, int group_min)
     return G < group_min ? group_min : G;
 }
 
-// Handles swept in bands of stages (bands.hip): every instance narrow (the
-// widths a band takes) and at most kBandChains chains in all.  The bands save
-// launches and latency, not bandwidth: per sweep against one launch per stage
-// (MI355X) 16 us against 46 on the 8-scenario tree with nx=4, nu=2; 62 against
-// 134 on the 4,095-node two-mode tree with nx=10, nu=4; 76 against 91 on 2,000
-// scenarios of 6 stages with nx=20, nu=10; level at 1,000 to 2,000 scenarios of
-// 15 stages of those blocks.  Wider blocks lose (nx=40, nu=20: 180 us against
-// 140: a lane group's rows are then one long serial product), and so does a
-// handle where wide instances need the per-stage launches anyway.  Chains of
-// more than kBandChainStages stages below s* stay with the chain kernel, whose
+// Handles swept in bands of stages (bands.hip): every instance with stages
+// above s* narrow (the widths a band takes) and at most kBandChains chains in
+// all.  The bands save launches and latency, not bandwidth: per sweep against
+// one launch per stage (MI355X) 16 us against 46 on the 8-scenario tree with
+// nx=4, nu=2; 62 against 134 on the 4,095-node two-mode tree with nx=10, nu=4;
+// 76 against 91 on 2,000 scenarios of 6 stages with nx=20, nu=10.
+// Wider blocks lose (nx=40, nu=20: 180 us against 140: a lane group's rows are
+// then one long serial product), and so does a handle where wide instances
+// need the per-stage launches anyway.
+constexpr long long kBandChains = 8192;
+// Chains of more stages below s* than this stay with the chain kernel, whose
 // steps cost less there (129 us against 152 for a sweep of 243 chains of 10
 // stages with nx=20); shorter ones save its two launches.
-constexpr long long kBandChains = 8192;
 constexpr int kBandChainStages = 3;
+// ... and of more than this where the chain kernel reads two rows of the
+// feedback matrices per load (16 lanes a chain, nx, nu <= 16) and a node has
+// 36 rows or more to read (nx + 2 nu), where its shorter steps tell.  Trees of 3
+// chain stages, us per sweep by bands / by chain kernels: nx = nu = 16, 1,000
+// trees of 2 scenarios 45.8 / 40.0, 100 of 8 43.6 / 36.8; nx=16, nu=10 36.6 / 33.7
+// (100 of 8) but nx=16, nu=8 30.3 / 32.1; 2 chain stages, nx = nu = 16, 1,000 trees
+// of 2 35.8 / 34.5, 100 trees 23.6 / 28.0.
+constexpr int kBandChainStagesPairs = 2;
+constexpr int kBandRowsPairs = 36;
+// An instance of a single scenario has one node a stage, which fills a quarter of
+// a band's wavefront at 16 lanes a node; a chain wavefront takes four of them.
+// With few of them that does not matter (nx=20, nu=10, 400 instances of 3
+// stages: 24.1 us by bands, 25.7 by chain kernels), with many it does (700: 31.1 /
+// 27.5, 8,000: 180 / 160; nx = nu = 16, 256 instances of 2 stages: 17.5 / 17.2,
+// 1,000: 24.0 / 17.7).  At 8 lanes a node the bands won at every count.  Most
+// stages of all such instances together that go with the bands, and the same
+// where the chain kernel's steps are the short ones above:
+constexpr long long kBandPathStages = 1200, kBandPathStagesPairs = 512;
 
 // Work lists of a sweep: the chains, one plan per lane-group width (each item
 // a wavefront's worth of consecutive chains of one instance; the costliest
@@ -726,7 +744,16 @@ int build_schedule(tree_factors *f)
     int max_sstar = 0, max_ldM = 0;
     // launch form 0: the stages above s* in bands, and a short chain part with them
     std::vector<std::vector<int>> cuts(f->ninst);
-    auto band_last = [](const InstDesc &I) { return I.N - I.sstar <= kBandChainStages ? I.N : I.sstar; };
+    long long path_stages = 0;
+    for (const InstDesc &I : f->inst)
+        if (I.nchains == 1 && I.ldM > 16) path_stages += I.N;
+    auto band_last = [&](const InstDesc &I) {
+        const bool pairs = I.ldM > 16 && I.nx <= 16 && I.nu <= 16 && I.nx + 2 * I.nu >= kBandRowsPairs;
+        const int most = pairs ? kBandChainStagesPairs : kBandChainStages;
+        const bool path = I.ldM > 16 && I.nchains == 1 &&
+                          path_stages > (pairs ? kBandPathStagesPairs : kBandPathStages);
+        return I.N - I.sstar <= most && !path ? I.N : I.sstar;
+    };
     if (f->trunk_fused == 0) {
         long long nchains = 0;
         for (const InstDesc &I : f->inst) nchains += I.nchains;
@@ -735,7 +762,7 @@ int build_schedule(tree_factors *f)
             const InstDesc &I = f->inst[b];
             if (b > 0 && f->shared > 1) cuts[b] = cuts[0];
             else cuts[b] = band_cuts(I, f->sp_pool.data() + I.sp, f->cp_pool.data() + I.cp, band_last(I));
-            all = !cuts[b].empty();
+            all = !cuts[b].empty() || I.sstar == 0;    // no stage above s*: chain kernels alone
         }
         if (!all) cuts.assign(f->ninst, {});
     }
@@ -795,8 +822,8 @@ int build_schedule(tree_factors *f)
         lv.items = arena.put(items);
         f->levels.push_back(lv);
         if (f->trunk_fused <= 2) {
-            // the nodes of the instances that are not swept in bands; in mode 2
-            // lane groups for the narrow ones, workgroups for the rest
+            // where nothing is swept in bands: workgroups for the nodes; in mode
+            // 2 lane groups for those of narrow instances, workgroups for the rest
             LevelPlan &L = f->levels.back();
             std::vector<Item> wide;
             std::map<int, std::vector<Item>> groups;

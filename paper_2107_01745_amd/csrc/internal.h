@@ -82,7 +82,7 @@ struct ChainPlan {
 };
 
 // One launch of the per-stage kernels: all (instance, node) pairs of one
-// stage, and how the nodes of the instances that are not swept in bands run:
+// stage, and how its nodes run on a handle that is not swept in bands:
 // workgroups of wide_nw wavefronts per node, or (trunk mode 2) lane-group items
 // of kWave/G consecutive nodes of one instance with nx + nu <= 64.
 struct LevelPlan {

@@ -1624,9 +1624,9 @@ static void launch_trunk_fused(bool backward, const SweepArgs &a, const tree_fac
     }
 }
 
-// One stage above s* of the instances that are not swept in bands: per-node
-// workgroups for every node, or (trunk mode 2) lane groups for the narrow
-// instances' nodes plus workgroups for the rest.
+// One stage above s* of a handle that is not swept in bands (no lists
+// otherwise): per-node workgroups for every node, or (trunk mode 2) lane groups
+// for the narrow instances' nodes plus workgroups for the rest.
 template <int NRHS, int CH>
 static void launch_level(bool backward, const SweepArgs &a, const tree_factors *f, const LevelPlan &lv, int ldM,
                          int qs, int ldu, hipStream_t st)

@@ -60,3 +60,32 @@ def test_sweep_in_place_on_a_batch():
                 assert both(sweep(tf, nrhs)[1])
             tf.free()
     """)
+
+
+def test_which_chains_go_with_the_bands():
+    """Chains below s* run in the bands where they are short, and in the chain kernels where those are
+    the faster: at 16 lanes a node, many instances of one scenario, or long rows read in pairs.  An
+    instance without a stage above s* does not send the others back to a launch per stage."""
+    hostsim.run("""
+        def kinds(*probs):
+            tf = factor(*probs)
+            rc, names = sweep(tf)
+            tf.free()
+            assert rc == 0
+            return sorted({re.match("band|narrow_chain|[a-z]+_chain|[a-z]+_trunk|narrow_level", n).group(0) for n in names})
+
+        one = lambda nx, nu, N: problem([1] * N, nx, nu)
+        assert kinds(*[one(4, 2, 3)] * 500) == ["band"]
+        assert kinds(*[one(20, 10, 3)] * 400) == ["band"]
+        assert kinds(*[one(20, 10, 3)] * 401) == ["narrow_chain"]
+        assert kinds(*[one(16, 16, 2)] * 256) == ["band"]
+        assert kinds(*[one(16, 16, 2)] * 257) == ["narrow_chain"]
+        assert kinds(one(16, 16, 3)) == ["narrow_chain"]
+        for nx, nu, tail, with_bands in ((16, 16, 3, False), (16, 16, 2, True), (16, 9, 3, True), (16, 10, 3, False),
+                                         (17, 15, 3, True), (17, 15, 4, False), (8, 8, 3, True), (8, 8, 4, False)):
+            got = kinds(problem([2, 2] + [1] * tail, nx, nu))
+            assert got == (["band"] if with_bands else ["band", "narrow_chain"]), (nx, nu, tail, got)
+        # a mixed handle
+        assert kinds(problem([3, 3], 4, 2), one(4, 2, 9)) == ["band", "narrow_chain"]
+        assert kinds(problem([3, 3], 4, 2), problem([2, 1], 40, 20)) == ["bwd_trunk", "fwd_trunk", "narrow_chain"]
+    """)
