@@ -9,7 +9,7 @@
 // scalars (residual norms, curvature test, L-BFGS coefficients, the accepted
 // step) are reduced and decided on the device by single-block "finalize"
 // kernels, so the host only reads a stop flag every check_every iterations,
-// with the next iteration already queued.
+// while the device works on.
 // Once the flag is set every remaining kernel returns immediately.
 //
 // Vector passes (grid-stride over the m dual rows, row r of node i scaled by
@@ -1118,7 +1118,16 @@ struct IterArgs {
     int div_due, backtrack;
     double *trace;
     int trace_iters;
+    bool poll;               // the host waits for this iteration's count of finished instances
 };
+
+// Requests the count of finished instances for the host, which waits for the
+// event.
+hipError_t enqueue_poll(const SolverWS &w, hipStream_t st)
+{
+    const hipError_t e = hipMemcpyAsync(w.ndone_host, w.ndone, sizeof(int), hipMemcpyDeviceToHost, st);
+    return e != hipSuccess ? e : hipEventRecord(w.polled, st);
+}
 
 // Infeasibility test of the iterate y (after fin_resid): the change since
 // the last test, its homogeneous sweep into hd, the reductions and the
@@ -1170,6 +1179,7 @@ hipError_t enqueue_iteration(const tree_factors *f, const IterArgs &it, hipStrea
         hipLaunchKernelGGL((resid_kernel<true, MEMCAP>), grid, blk, 0, st, a);
         hipLaunchKernelGGL(fin_resid_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, 1, a.ndone, it.div_due);
         if (it.div_due && (e = enqueue_div_test(f, y, k == 0, st))) return e;
+        if (it.poll && (e = enqueue_poll(w, st))) return e;
         VecArgs cb = a;
         cb.g = r;           // g = R
         cb.r = w.d;         // output direction
@@ -1180,6 +1190,7 @@ hipError_t enqueue_iteration(const tree_factors *f, const IterArgs &it, hipStrea
         hipLaunchKernelGGL((resid_kernel<false, 0>), grid, blk, 0, st, a);
         hipLaunchKernelGGL(fin_resid_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, 0, a.ndone, it.div_due);
         if (it.div_due && (e = enqueue_div_test(f, y, k == 0, st))) return e;
+        if (it.poll && (e = enqueue_poll(w, st))) return e;
         // grad phi = R + lambda s H xhat(s R)
         if ((e = dual_sweep(f, 0, nullptr, r, 0, hr, 0, done_flags(ctl), 1, st, active))) return e;
         VecArgs ga = a;
@@ -1217,6 +1228,7 @@ hipError_t enqueue_gpad(const tree_factors *f, const IterArgs &it, hipStream_t s
     hipLaunchKernelGGL((resid_kernel<false, 0>), grid, blk, 0, st, a);
     hipLaunchKernelGGL(fin_resid_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, 0, a.ndone, it.div_due);
     if (it.div_due && (e = enqueue_div_test(f, wv, it.k == 0, st))) return e;
+    if (it.poll && (e = enqueue_poll(w, st))) return e;
     hipLaunchKernelGGL(fin_gpad_kernel, fgrid, dim3(64), 0, st, ctl);
     VecArgs ua = a;
     ua.g = wv; ua.r = r; ua.yn = ym;
@@ -1363,27 +1375,37 @@ int solve(const tree_factors *fc, const double *x0, const solver_opts *opts_in, 
     IterFn iter = method == 2 ? enqueue_gpad : pick_iter(o.mem, o.nu_max);
     // each halving of lambda costs one update that does not count
     const int last = o.max_iter + (backtrack ? kBtMax + 1 : 0);
-    int k = 0, ndone = 0, ahead = 0;
+    int k = 0, ndone = 0, ahead = 0, polls = 0;
     // instances finished by the last check are skipped by the sweeps (the
-    // count may lag behind by check_every iterations and one; it only grows)
-    auto enqueue = [&]() -> hipError_t {
+    // count may lag behind by check_every iterations, in GPAD by one more; it
+    // only grows)
+    auto enqueue = [&](bool poll) -> hipError_t {
         IterArgs it{x0, {ybuf[0], ybuf[1]}, k, method, f->ninst - ndone,
-                    div_window > 0 && k % div_window == 0, backtrack, o.trace, o.trace_iters};
+                    div_window > 0 && k % div_window == 0, backtrack, o.trace, o.trace_iters, poll};
         ++k;
         return iter(f, it, st);
     };
+    // The host reads the count while the device has work (36 us an iteration
+    // otherwise).  Instances finish at the residual, in the middle of an
+    // iteration, so the count is requested there and the host waits with the rest
+    // of the iteration queued behind it; a solve that ends has queued no launch for
+    // the poll.  GPAD has only two short kernels behind its residual: from its
+    // second poll on, one more iteration goes in before the host waits (whose
+    // kernels find every instance finished if the count ends the solve).
+    // Accepted at the first residual, against always queueing one more: MINFBE on
+    // the 6,485-node tree with nx=50, nu=30 588 us (660), on the 4,095-node
+    // two-mode tree 197 (237), GPAD there 183 (195); 20 iterations of NAMA on an
+    // 8-scenario tree with nx=4, nu=2 1,612 (1,559), elsewhere the same.
     while (ndone < f->ninst && k <= last) {
+        const bool inside = method != 2 || polls == 0;
         hipError_t e = hipSuccess;
-        for (int c = ahead; c < o.check_every && k <= last && e == hipSuccess; ++c) e = enqueue();
-        if (e == hipSuccess) e = hipMemcpyAsync(f->sws.ndone_host, w.ndone, sizeof(int), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipEventRecord(f->sws.polled, st);
-        // one more iteration goes in before the host waits for the count, so
-        // the device has work while it does (36 us a poll otherwise); if the
-        // count ends the solve, that iteration's kernels find every instance
-        // finished and return
+        for (int c = ahead; c < o.check_every && k <= last && e == hipSuccess; ++c)
+            e = enqueue(inside && (c + 1 == o.check_every || k == last));
+        if (e == hipSuccess && !inside) e = enqueue_poll(w, st);
         ahead = 0;
-        if (e == hipSuccess && k <= last) {
-            e = enqueue();
+        ++polls;
+        if (e == hipSuccess && !inside && k <= last) {
+            e = enqueue(false);
             ahead = 1;
         }
         if (e != hipSuccess) {
@@ -1391,8 +1413,8 @@ int solve(const tree_factors *fc, const double *x0, const solver_opts *opts_in, 
             set_error(std::string("solve: ") + hipGetErrorString(e));
             return STOTREE_ERR_DEVICE;
         }
-        STOTREE_HIP(hipEventSynchronize(f->sws.polled));
-        ndone = *f->sws.ndone_host;
+        STOTREE_HIP(hipEventSynchronize(w.polled));
+        ndone = *w.ndone_host;
     }
     if (method != 2) {
         // last iterate of every instance into y_io (GPAD keeps it there)

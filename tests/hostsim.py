@@ -33,7 +33,7 @@ def launches(log=None):
     for ln in calls() if log is None else log:
         if ln.startswith("launch "):
             mangled = ln.split()[1]
-            m = re.search(r"[0-9]+([a-z0-9_]+_kernel)(I\\S*?E)?Ev", mangled)
+            m = re.search(r"[0-9]+([a-z][a-z0-9_]*_kernel)(I\\S*?E)?E[vNPil]", mangled)
             out.append(m.group(1) + (m.group(2) or "") if m else mangled)
     return out
 

@@ -1,0 +1,71 @@
+"""The solvers' host loop (no GPU: kernel launches are logged and not run; the test plays the device's
+part of counting finished instances)."""
+import hostsim
+
+SETUP = """
+    # the residual's decision number `stop` ends the solve: it counts every instance as finished
+    state = dict(seen=0, stop=0, ninst=1)
+
+    @C.CFUNCTYPE(None, C.c_char_p, C.POINTER(C.c_void_p))
+    def on_launch(name, args):
+        if b"fin_resid_kernel" in name:
+            if state["seen"] == state["stop"]:
+                ndone = C.cast(args[4], C.POINTER(C.c_void_p))[0]      # fin_resid_kernel(ctl, part, nblocks, with_pair, ndone, div_due)
+                C.cast(ndone, C.POINTER(C.c_int))[0] = state["ninst"]
+            state["seen"] += 1
+
+    fake.fake_on_launch(on_launch)
+    SOLVERS = dict(nama=L.nama_solve, minfbe=L.minfbe_solve, gpad=L.gpad_solve)
+
+    def solve(tf, method, stop, check_every=1, max_iter=1000):
+        state.update(seen=0, stop=stop, ninst=tf.ninst)
+        info = st.SolverInfo()
+        opts = st.make_opts(lam=0.1, eps=1e-6, max_iter=max_iter, check_every=check_every, div_window=-1)
+        calls()
+        rc = SOLVERS[method](tf.handle, buf(tf.x0_len), C.byref(opts), buf(tf.m), buf(tf.x_len), buf(tf.u_len),
+                             C.byref(info), None)
+        assert rc >= 0, (rc, st.stotree_last_error())
+        return calls()
+"""
+
+
+def _run(body):
+    import textwrap
+    hostsim.run(textwrap.dedent(SETUP) + textwrap.dedent(body))
+
+
+def test_a_solve_that_stops_queues_no_further_iteration():
+    """The residual of iteration `stop` ends the solve: NAMA and MINFBE queue the iterations up to that
+    one and nothing of the next; GPAD at most one more, and none at the first residual.  The number of
+    residuals seen is the number of iterations queued."""
+    _run("""
+        for prob in (problem([2, 2, 2], 4, 2), problem([2, 2, 1, 1], 40, 20)):
+            tf = factor(prob)
+            for method in SOLVERS:
+                for stop in (0, 1, 2, 5):
+                    solve(tf, method, stop)
+                    queued = stop + 1 + (method == "gpad" and stop > 0)
+                    assert state["seen"] == queued, (method, stop, state["seen"])
+                solve(tf, method, stop=4, check_every=3)
+                assert state["seen"] == (7 if method == "gpad" else 6), (method, state)
+                # never stopped by the device: max_iter + 1 residuals
+                solve(tf, method, stop=10 ** 9, max_iter=7)
+                assert state["seen"] == 8, (method, state)
+            tf.free()
+    """)
+
+
+def test_the_host_waits_with_work_queued_behind_the_count():
+    """NAMA and MINFBE: between the request of the count and the host's wait lies the second half of the
+    iteration."""
+    _run("""
+        tf = factor(problem([2, 2, 2], 4, 2))
+        for method in ("nama", "minfbe"):
+            log = solve(tf, method, 3)
+            waits = [k for k, ln in enumerate(log) if ln == "event sync"]
+            assert len(waits) == 4
+            for w in waits:
+                r = max(k for k in range(w) if log[k] == "event record")
+                between = launches(log[r:w])
+                assert any(n.startswith("ls_kernel") for n in between) and "update_kernel" in between, between
+    """)
