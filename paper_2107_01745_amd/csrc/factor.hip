@@ -685,8 +685,6 @@ void free_tree(tree_factors *f)
                     (void *)f->map_ws})
         if (p) (void)hipFree(p);
     if (f->d_inst_xu && f->d_inst_xu != f->d_inst) (void)hipFree(f->d_inst_xu);
-    if (f->sws.ndone_host) (void)hipHostFree(f->sws.ndone_host);
-    if (f->sws.polled) (void)hipEventDestroy(f->sws.polled);
     for (void *p : {(void *)f->trunk_cnt, (void *)f->Pcal, (void *)f->sched})
         if (p) (void)hipFree(p);
     delete f;

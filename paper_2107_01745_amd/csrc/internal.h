@@ -137,8 +137,6 @@ struct SolverWS {
     void *ctl;                       // device array of per-instance control blocks
     int *blk;                        // device: per block {instance, local block, blocks of the instance}
     int *ndone;                      // device counter of finished instances
-    int *ndone_host = nullptr;       // pinned: its value at the last polls
-    hipEvent_t polled = nullptr;     // the poll's copy has arrived
     std::vector<int> blk_first;      // host: first block of each instance
 };
 

@@ -39,6 +39,7 @@
 #include <cfloat>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <vector>
 
 #include "internal.h"
@@ -1118,15 +1119,78 @@ struct IterArgs {
     int div_due, backtrack;
     double *trace;
     int trace_iters;
-    bool poll;               // the host waits for this iteration's count of finished instances
+    const struct Poll *poll;  // the host waits for this iteration's count of finished instances (or null)
 };
 
-// Requests the count of finished instances for the host, which waits for the
-// event.
-hipError_t enqueue_poll(const SolverWS &w, hipStream_t st)
+// Where a solve's host loop receives the count of finished instances: pinned
+// memory and an event, taken from a pool for the length of a call (a new pair
+// costs two allocations, and a controller that linearises its model again makes
+// a new handle for every solve).  The pool keeps at most kPollKept pairs for the
+// process and may be used by several threads at once; pairs belong to a device.
+struct Poll {
+    int dev = -1;
+    int *count = nullptr;
+    hipEvent_t ev = nullptr;
+    mutable bool pending = false;        // a copy into count may be on its way
+};
+constexpr size_t kPollKept = 16;
+struct PollPool {
+    std::mutex mu;
+    std::vector<Poll> kept;
+};
+PollPool &poll_pool()
 {
-    const hipError_t e = hipMemcpyAsync(w.ndone_host, w.ndone, sizeof(int), hipMemcpyDeviceToHost, st);
-    return e != hipSuccess ? e : hipEventRecord(w.polled, st);
+    static PollPool *p = new PollPool;   // not torn down: the runtime may be gone by then
+    return *p;
+}
+struct PollLease : Poll {
+    int take()
+    {
+        STOTREE_HIP(hipGetDevice(&dev));
+        PollPool &p = poll_pool();
+        {
+            std::lock_guard<std::mutex> lock(p.mu);
+            for (size_t k = p.kept.size(); k-- > 0;)
+                if (p.kept[k].dev == dev) {
+                    static_cast<Poll &>(*this) = p.kept[k];
+                    p.kept.erase(p.kept.begin() + (long)k);
+                    return STOTREE_OK;
+                }
+        }
+        STOTREE_HIP(hipHostMalloc(reinterpret_cast<void **>(&count), sizeof(int), 0));
+        STOTREE_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+        return STOTREE_OK;
+    }
+    hipError_t wait()
+    {
+        const hipError_t e = hipEventSynchronize(ev);
+        if (e == hipSuccess) pending = false;
+        return e;
+    }
+    ~PollLease()
+    {
+        // (a solve that failed may leave a copy on its way)
+        if (pending && wait() != hipSuccess) return;
+        if (count && ev) {
+            PollPool &p = poll_pool();
+            std::lock_guard<std::mutex> lock(p.mu);
+            if (p.kept.size() < kPollKept) {
+                p.kept.push_back(*this);
+                return;
+            }
+        }
+        if (count) (void)hipHostFree(count);
+        if (ev) (void)hipEventDestroy(ev);
+    }
+};
+
+// Requests the count for the host, which waits for the event.
+hipError_t enqueue_poll(const Poll &p, const SolverWS &w, hipStream_t st)
+{
+    const hipError_t e = hipMemcpyAsync(p.count, w.ndone, sizeof(int), hipMemcpyDeviceToHost, st);
+    if (e != hipSuccess) return e;
+    p.pending = true;
+    return hipEventRecord(p.ev, st);
 }
 
 // Infeasibility test of the iterate y (after fin_resid): the change since
@@ -1179,7 +1243,7 @@ hipError_t enqueue_iteration(const tree_factors *f, const IterArgs &it, hipStrea
         hipLaunchKernelGGL((resid_kernel<true, MEMCAP>), grid, blk, 0, st, a);
         hipLaunchKernelGGL(fin_resid_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, 1, a.ndone, it.div_due);
         if (it.div_due && (e = enqueue_div_test(f, y, k == 0, st))) return e;
-        if (it.poll && (e = enqueue_poll(w, st))) return e;
+        if (it.poll && (e = enqueue_poll(*it.poll, w, st))) return e;
         VecArgs cb = a;
         cb.g = r;           // g = R
         cb.r = w.d;         // output direction
@@ -1190,7 +1254,7 @@ hipError_t enqueue_iteration(const tree_factors *f, const IterArgs &it, hipStrea
         hipLaunchKernelGGL((resid_kernel<false, 0>), grid, blk, 0, st, a);
         hipLaunchKernelGGL(fin_resid_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, 0, a.ndone, it.div_due);
         if (it.div_due && (e = enqueue_div_test(f, y, k == 0, st))) return e;
-        if (it.poll && (e = enqueue_poll(w, st))) return e;
+        if (it.poll && (e = enqueue_poll(*it.poll, w, st))) return e;
         // grad phi = R + lambda s H xhat(s R)
         if ((e = dual_sweep(f, 0, nullptr, r, 0, hr, 0, done_flags(ctl), 1, st, active))) return e;
         VecArgs ga = a;
@@ -1228,7 +1292,7 @@ hipError_t enqueue_gpad(const tree_factors *f, const IterArgs &it, hipStream_t s
     hipLaunchKernelGGL((resid_kernel<false, 0>), grid, blk, 0, st, a);
     hipLaunchKernelGGL(fin_resid_kernel, fgrid, dim3(kFin), 0, st, ctl, a.part, a.nblocks, 0, a.ndone, it.div_due);
     if (it.div_due && (e = enqueue_div_test(f, wv, it.k == 0, st))) return e;
-    if (it.poll && (e = enqueue_poll(w, st))) return e;
+    if (it.poll && (e = enqueue_poll(*it.poll, w, st))) return e;
     hipLaunchKernelGGL(fin_gpad_kernel, fgrid, dim3(64), 0, st, ctl);
     VecArgs ua = a;
     ua.g = wv; ua.r = r; ua.yn = ym;
@@ -1337,8 +1401,8 @@ int solve(const tree_factors *fc, const double *x0, const solver_opts *opts_in, 
     int rc = ensure_solver_ws(f, WsNeed{o.mem, method == 0, div_window > 0, backtrack == 1});
     if (rc) return rc;
     if ((rc = ensure_sweep_ws(f, 2))) return rc;
-    if (!f->sws.ndone_host) STOTREE_HIP(hipHostMalloc(reinterpret_cast<void **>(&f->sws.ndone_host), sizeof(int), 0));
-    if (!f->sws.polled) STOTREE_HIP(hipEventCreateWithFlags(&f->sws.polled, hipEventDisableTiming));
+    PollLease poll;
+    if ((rc = poll.take())) return rc;
     const SolverWS &w = f->sws;
     Ctl *dctl = reinterpret_cast<Ctl *>(w.ctl);
     std::vector<Ctl> h = fresh_ctl(f);
@@ -1379,9 +1443,9 @@ int solve(const tree_factors *fc, const double *x0, const solver_opts *opts_in, 
     // instances finished by the last check are skipped by the sweeps (the
     // count may lag behind by check_every iterations, in GPAD by one more; it
     // only grows)
-    auto enqueue = [&](bool poll) -> hipError_t {
+    auto enqueue = [&](bool polled) -> hipError_t {
         IterArgs it{x0, {ybuf[0], ybuf[1]}, k, method, f->ninst - ndone,
-                    div_window > 0 && k % div_window == 0, backtrack, o.trace, o.trace_iters, poll};
+                    div_window > 0 && k % div_window == 0, backtrack, o.trace, o.trace_iters, polled ? &poll : nullptr};
         ++k;
         return iter(f, it, st);
     };
@@ -1401,7 +1465,7 @@ int solve(const tree_factors *fc, const double *x0, const solver_opts *opts_in, 
         hipError_t e = hipSuccess;
         for (int c = ahead; c < o.check_every && k <= last && e == hipSuccess; ++c)
             e = enqueue(inside && (c + 1 == o.check_every || k == last));
-        if (e == hipSuccess && !inside) e = enqueue_poll(w, st);
+        if (e == hipSuccess && !inside) e = enqueue_poll(poll, w, st);
         ahead = 0;
         ++polls;
         if (e == hipSuccess && !inside && k <= last) {
@@ -1413,8 +1477,8 @@ int solve(const tree_factors *fc, const double *x0, const solver_opts *opts_in, 
             set_error(std::string("solve: ") + hipGetErrorString(e));
             return STOTREE_ERR_DEVICE;
         }
-        STOTREE_HIP(hipEventSynchronize(w.polled));
-        ndone = *w.ndone_host;
+        STOTREE_HIP(poll.wait());
+        ndone = *poll.count;
     }
     if (method != 2) {
         // last iterate of every instance into y_io (GPAD keeps it there)

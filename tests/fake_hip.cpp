@@ -6,6 +6,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -19,8 +20,8 @@ std::map<const void *, std::string> &names()
 struct Config { Dim3 grid, block; size_t lds; void *stream; };
 std::vector<Config> &configs()
 {
-    static auto *v = new std::vector<Config>();
-    return *v;
+    static thread_local std::vector<Config> v;
+    return v;
 }
 std::string &calls()
 {
@@ -30,7 +31,12 @@ std::string &calls()
 int fail_mallocs_from = -1;          // hipMalloc fails from this one on (counted down; -1: never)
 float (*elapsed_cb)() = nullptr;
 void (*launch_cb)(const char *, void **) = nullptr;
-void note(const std::string &s) { calls() += s + "\n"; }
+std::mutex mu;
+void note(const std::string &s)
+{
+    std::lock_guard<std::mutex> lock(mu);
+    calls() += s + "\n";
+}
 void *block(size_t n) { return std::calloc(1, n ? n : 1); }
 constexpr int kOutOfMemory = 2;
 }  // namespace

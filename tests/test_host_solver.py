@@ -69,3 +69,42 @@ def test_the_host_waits_with_work_queued_behind_the_count():
                 between = launches(log[r:w])
                 assert any(n.startswith("ls_kernel") for n in between) and "update_kernel" in between, between
     """)
+
+
+def test_new_handles_need_no_new_pinned_memory():
+    """A controller that factors and solves again at every instant: pinned memory and events are
+    allocated for the first solve only; concurrent solves get their own, and no more than 16 are kept."""
+    _run("""
+        import threading
+        count = lambda log: sum(ln.startswith(("hostmalloc", "event create")) for ln in log)
+        total = 0
+        for _ in range(20):
+            tf = factor(problem([2, 2], 3, 1))
+            total += count(solve(tf, "nama", 1))
+            tf.free()
+        assert total == 2, total
+        # 40 threads inside a solve at once
+        inside = threading.Barrier(40)
+
+        @C.CFUNCTYPE(None, C.c_char_p, C.POINTER(C.c_void_p))
+        def meet(name, args):
+            if b"gather_final" in name:
+                inside.wait(60)
+
+        fake.fake_on_launch(meet)
+        tfs = [factor(problem([2, 2], 3, 1)) for _ in range(40)]
+        opts = st.make_opts(lam=0.1, max_iter=0, div_window=-1)
+        args = [[C.c_void_p(v) for v in (buf(t.x0_len), buf(t.m), buf(t.x_len), buf(t.u_len))] for t in tfs]
+        def go(t, a):
+            info = st.SolverInfo()
+            assert L.nama_solve(t.handle, a[0], C.byref(opts), a[1], a[2], a[3], C.byref(info), None) == 1
+        def round_():
+            th = [threading.Thread(target=go, args=ta) for ta in zip(tfs, args)]
+            for t in th: t.start()
+            for t in th: t.join()
+        calls()
+        round_()
+        assert count(calls()) == 2 * 39
+        round_()
+        assert count(calls()) == 2 * 24          # 16 kept
+    """)
