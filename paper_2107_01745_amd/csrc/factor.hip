@@ -767,11 +767,13 @@ int build_schedule(tree_factors *f)
     build_bands(f, cuts, arena);
     std::map<int, std::vector<std::pair<double, Item>>> by_G;
     std::map<int, int> ldq_G;
+    f->chained.assign(f->ninst, 0);
     for (int b = 0; b < f->ninst; ++b) {
         const InstDesc &I = f->inst[b];
         max_sstar = std::max(max_sstar, I.sstar);
         max_ldM = std::max(max_ldM, I.ldM);
         if (I.sstar >= I.N || (!cuts[b].empty() && band_last(I) == I.N)) continue;
+        f->chained[b] = 1;
         const int G = chain_group(I.ldM, f->group_min);
         const int per = kWave / G;
         ldq_G[G] = std::max(ldq_G[G], I.ldM);

@@ -110,6 +110,7 @@ struct BandPlan {
 struct Schedule {
     char *sched = nullptr;
     std::vector<ChainPlan> chains;   // stages s*..N, one plan per lane-group width
+    std::vector<char> chained;       // per instance: its chains are in the plans above
     std::vector<LevelPlan> levels;   // stages 0..max(s*)-1
     std::vector<BandPlan> bands;     // narrow instances' stages, first band at the root
     int *band_tabs = nullptr;        // device: the subtrees' tables

@@ -46,12 +46,28 @@ bool valid_knobs(const int32_t *k)
     return g && o && t && m && p;
 }
 
-// Lane-group width of every instance under group_min g (equal vectors give
-// identical chain work lists).
-std::vector<int> groups_of(const tree_factors *f, int g)
+// What of a schedule the first three knobs reach: the instances whose chains
+// (in launch form 2 also whose stages) run in lane groups, and whether stages
+// run as workgroups per node.  Bands ignore all three.
+struct Reach {
+    std::vector<char> grouped;           // per instance
+    bool chains, stages;
+};
+Reach reach_of(const tree_factors *f)
+{
+    Reach r{f->chained, !f->chains.empty(), f->fused_bwd.count > 0 || !f->rest_levels.empty()};
+    for (const LevelPlan &lv : f->levels) r.stages |= f->trunk_fused <= 2 && lv.wide_count > 0;
+    if (f->trunk_fused == 2)
+        for (size_t b = 0; b < f->inst.size(); ++b) r.grouped[b] |= f->inst[b].sstar > 0;
+    return r;
+}
+
+// Lane-group width of every grouped instance under group_min g (equal vectors
+// give identical work lists).
+std::vector<int> groups_of(const tree_factors *f, const Reach &r, int g)
 {
     std::vector<int> v;
-    for (const InstDesc &I : f->inst) v.push_back(I.sstar < I.N ? chain_group(I.ldM, g) : 0);
+    for (size_t b = 0; b < f->inst.size(); ++b) v.push_back(r.grouped[b] ? chain_group(f->inst[b].ldM, g) : 0);
     return v;
 }
 
@@ -126,13 +142,20 @@ int autotune(tree_factors *f, int nrhs, int reps, int32_t *knobs_out, double *ms
     if (shared) best[4] = kPanelMinMax;    // lane-group route while its knobs are tuned
     double best_ms = 0.0;
     rc = measure(best, &best_ms);
+    Reach reach = reach_of(f);
     const std::vector<std::vector<int>> values = {{8, 16, 32, 64}, {1, 0}, {16, 8, 4, 2}, {0, 2, 1, 3, 4}};
-    for (int knob = 0; knob < kKnobs - 1 && !rc; ++knob) {
+    // a handle swept in bands: the launch form first, since the other knobs
+    // change nothing there (a candidate with the same work lists is not timed: it
+    // could only win by noise, and would then stand in the forms where it counts)
+    const bool form_first = !f->bands.empty();
+    for (int step = 0; step < kKnobs - 1 && !rc; ++step) {
+        const int knob = form_first ? (step == 0 ? 3 : step - 1) : step;
         const int32_t start = best[knob];
         for (int v : values[knob]) {
             if (rc) break;
             if (v == start) continue;
-            if (knob == 0 && groups_of(f, v) == groups_of(f, best[0])) continue;
+            if (knob == 0 && groups_of(f, reach, v) == groups_of(f, reach, best[0])) continue;
+            if ((knob == 1 && !reach.chains) || (knob == 2 && !reach.stages)) continue;
             int32_t cand[kKnobs] = {best[0], best[1], best[2], best[3], best[4]};
             cand[knob] = v;
             double ms = 0.0;
@@ -140,6 +163,7 @@ int autotune(tree_factors *f, int nrhs, int reps, int32_t *knobs_out, double *ms
             if (!rc && ms < best_ms) {
                 best_ms = ms;
                 best[knob] = v;
+                reach = reach_of(f);
             }
         }
     }

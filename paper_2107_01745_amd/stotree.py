@@ -305,12 +305,13 @@ def sweep_schedule_get(tf: TreeFactors) -> tuple:
 
 def forest_signature(tf: TreeFactors, nrhs: int) -> str:
     """Key of the autotuning cache: the sizes of every instance, whether the
-    instances are copies of one factored tree, and nrhs."""
+    instances are copies of one factored tree, nrhs, and the number and
+    version of the knobs (2: launch form 0 sweeps narrow trees in bands)."""
     import hashlib
     h = hashlib.sha1()
     for d in tf.instances:
         h.update(repr((d["nx"], d["nu"], d["N"], d["V"], d["Vnl"], d["sstar"])).encode())
-    return f"{tf.ninst}x{h.hexdigest()[:16]}:shared{tf.shared}:nrhs{nrhs}:k5"
+    return f"{tf.ninst}x{h.hexdigest()[:16]}:shared{tf.shared}:nrhs{nrhs}:k5.2"
 
 
 def sweep_autotune(tf: TreeFactors, nrhs: int = 1, reps: int = 5, cache: str | None = None,

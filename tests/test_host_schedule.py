@@ -89,3 +89,38 @@ def test_which_chains_go_with_the_bands():
         assert kinds(problem([3, 3], 4, 2), one(4, 2, 9)) == ["band", "narrow_chain"]
         assert kinds(problem([3, 3], 4, 2), problem([2, 1], 40, 20)) == ["bwd_trunk", "fwd_trunk", "narrow_chain"]
     """)
+
+
+def test_autotune_leaves_knobs_without_effect():
+    """Lane group, chain order and wavefront cap change nothing where stages and chains run in bands: the
+    autotuner must not pick them on timing noise (here every later timing of the same work is a little
+    shorter), and a cached schedule from before the bands is not applied."""
+    hostsim.run("""
+        import json, os, tempfile
+        n = [0]
+
+        @C.CFUNCTYPE(C.c_float)
+        def elapsed():
+            names = launches()
+            n[0] += 1
+            bands = names and all(k.startswith(("band_kernel", "narrow_chain_kernel")) for k in names)
+            return (10.0 if bands else 1000.0) - 1e-3 * n[0]
+
+        fake.fake_on_elapsed(elapsed)
+        tf = factor(problem([2, 2, 1], 4, 2))                   # all in bands
+        assert st.sweep_autotune(tf, stream=0)["knobs"] == [8, 1, 16, 0, 16]
+        tf = factor(problem([2, 2] + [1] * 6, 4, 2))            # chains of their own: group and order count
+        k = st.sweep_autotune(tf, stream=0)["knobs"]
+        assert k[2:] == [16, 0, 16], k
+        tf = factor(problem([3, 3, 1, 1], 40, 20))              # no bands: every knob counts
+        k = st.sweep_autotune(tf, stream=0)["knobs"]
+        assert k[2] == 2 and k[3] != 0, k
+        # a cache written when launch form 0 was one launch per stage
+        tf = factor(problem([2, 2, 1], 4, 2))
+        cache = os.path.join(tempfile.mkdtemp(), "tune.json")
+        old_key = re.sub(r":k5.*", ":k5", st.forest_signature(tf, 1))
+        json.dump({old_key: {"knobs": [64, 0, 2, 0, 16], "ms": 1.0}}, open(cache, "w"))
+        rec = st.sweep_autotune(tf, cache=cache, stream=0)
+        assert not rec["cached"] and rec["knobs"] == [8, 1, 16, 0, 16], rec
+        assert st.sweep_autotune(tf, cache=cache, stream=0)["cached"]
+    """)
