@@ -807,61 +807,60 @@ int build_schedule(tree_factors *f)
         cp.items = arena.put(items);
         f->chains.push_back(cp);
     }
+    // a stage's whole list is read by the panel sweeps of many right-hand sides
+    // and, where nothing is swept in bands, by the workgroups of forms 0 and 1
+    const bool banded = !f->bands.empty();
+    const bool whole = (f->shared <= 1 && panel_tpw(f) > 0) || (!banded && f->trunk_fused <= 1);
     for (int t = 0; t < max_sstar; ++t) {
-        std::vector<Item> items;
+        LevelPlan lv{};
+        lv.t = t;
+        std::vector<Item> items, wide;
+        std::map<int, std::vector<Item>> groups;
+        std::map<int, int> gldq;
+        int wide_ldM = 2;
         for (int b = 0; b < f->ninst; ++b) {
             const InstDesc &I = f->inst[b];
             if (t >= I.sstar) continue;
             const int *sp = f->sp_pool.data() + I.sp;
-            for (int i = sp[t]; i < sp[t + 1]; ++i) items.push_back({b, i});
-        }
-        LevelPlan lv{};
-        lv.t = t;
-        lv.count = (int)items.size();
-        lv.nw = trunk_waves(lv.count, 2, max_ldM, f->trunk_cap);
-        lv.items = arena.put(items);
-        f->levels.push_back(lv);
-        if (f->trunk_fused <= 2) {
-            // where nothing is swept in bands: workgroups for the nodes; in mode
-            // 2 lane groups for those of narrow instances, workgroups for the rest
-            LevelPlan &L = f->levels.back();
-            std::vector<Item> wide;
-            std::map<int, std::vector<Item>> groups;
-            std::map<int, int> gldq;
-            int wide_ldM = 2;
-            for (int b = 0; b < f->ninst; ++b) {
-                const InstDesc &I = f->inst[b];
-                if (t >= I.sstar || !cuts[b].empty()) continue;
-                const int *sp = f->sp_pool.data() + I.sp;
-                const int G = chain_group(I.ldM, f->group_min);
-                if (f->trunk_fused != 2 || G == kWave) {
+            if (whole)
+                for (int i = sp[t]; i < sp[t + 1]; ++i) items.push_back({b, i});
+            const int G = chain_group(I.ldM, f->group_min);
+            if (f->trunk_fused != 2 || G == kWave) {
+                wide_ldM = std::max(wide_ldM, I.ldM);
+                if (f->trunk_fused == 2)
                     for (int i = sp[t]; i < sp[t + 1]; ++i) wide.push_back({b, i});
-                    wide_ldM = std::max(wide_ldM, I.ldM);
-                    continue;
-                }
-                gldq[G] = std::max(gldq[G], I.ldM);
-                for (int i = sp[t]; i < sp[t + 1]; i += kWave / G) groups[G].push_back({b, i});
+                continue;
             }
-            L.wide_count = (int)wide.size();
-            L.wide_nw = trunk_waves(L.wide_count, 2, wide_ldM, f->trunk_cap);
-            L.wide_items = arena.put(wide);
-            for (auto &kv : groups) {
-                ChainPlan g{};
-                g.G = kv.first;
-                g.CH = 1;
-                g.ldq = gldq[kv.first];
-                g.count = (int)kv.second.size();
-                g.items = arena.put(kv.second);
-                L.narrow.push_back(g);
-            }
+            // form 2: lane groups for the nodes of narrow instances
+            gldq[G] = std::max(gldq[G], I.ldM);
+            for (int i = sp[t]; i < sp[t + 1]; i += kWave / G) groups[G].push_back({b, i});
         }
+        lv.count = (int)items.size();
+        lv.items = arena.put(items);
+        if (!banded && f->trunk_fused <= 2) {
+            lv.wide_count = f->trunk_fused == 2 ? (int)wide.size() : lv.count;
+            lv.wide_items = f->trunk_fused == 2 ? arena.put(wide) : lv.items;
+            lv.wide_nw = trunk_waves(lv.wide_count, 2, wide_ldM, f->trunk_cap);
+        }
+        for (auto &kv : groups) {
+            ChainPlan g{};
+            g.G = kv.first;
+            g.CH = 1;
+            g.ldq = gldq[kv.first];
+            g.count = (int)kv.second.size();
+            g.items = arena.put(kv.second);
+            lv.narrow.push_back(g);
+        }
+        f->levels.push_back(lv);
         if (panel_inst < f->ninst) {
             const InstDesc &I = f->inst[0];
+            const int *sp = f->sp_pool.data() + I.sp;
+            std::vector<Item> first;
+            for (int i = sp[t]; i < sp[t + 1] && t < I.sstar; ++i) first.push_back({0, i});
             LevelPlan pl{};
             pl.t = t;
-            pl.nw = lv.nw;
-            pl.count = t < I.sstar ? f->sp_pool[I.sp + t + 1] - f->sp_pool[I.sp + t] : 0;
-            pl.items = arena.put(std::vector<Item>(items.begin(), items.begin() + pl.count));
+            pl.count = (int)first.size();
+            pl.items = arena.put(first);
             f->panel_levels.push_back(pl);
         }
     }
@@ -919,8 +918,8 @@ int build_schedule(tree_factors *f)
             f->rest_levels.push_back(lv);
         }
     }
-    // one-launch backward trunk: its entry nodes and the per-node counters
-    {
+    // one-launch backward trunk: its entry nodes
+    if (f->trunk_fused == 1) {
         std::vector<Item> entry;
         for (int b = 0; b < f->ninst; ++b) {
             const InstDesc &I = f->inst[b];
@@ -941,8 +940,8 @@ int build_schedule(tree_factors *f)
         else e = hipMemcpy(f->sched, arena.host.data(), arena.host.size(), hipMemcpyHostToDevice);
     }
     each_list(f, [&](auto *&p) { ListArena::settle(p, f->sched); });
-    if (e == hipSuccess && f->trunk_entry.count > 0) {
-        // counters, flags and the fused launches' error word start at zero
+    if (e == hipSuccess && max_sstar > 0 && (f->trunk_fused == 1 || f->trunk_fused >= 3)) {
+        // per-node counters, flags and the fused launches' error word start at zero
         if (!f->trunk_cnt) e = hipMalloc(&f->trunk_cnt, sizeof(int) * (size_t)(f->V_tot + 1));
         if (e == hipSuccess) e = hipMemset(f->trunk_cnt, 0, sizeof(int) * (size_t)(f->V_tot + 1));
     }

@@ -82,9 +82,10 @@ struct ChainPlan {
 };
 
 // One launch of the per-stage kernels: all (instance, node) pairs of one
-// stage, and how its nodes run on a handle that is not swept in bands:
-// workgroups of wide_nw wavefronts per node, or (trunk mode 2) lane-group items
-// of kWave/G consecutive nodes of one instance with nx + nu <= 64.
+// stage (items; where panel sweeps or the workgroups read them), and how its
+// nodes run on a handle that is not swept in bands: workgroups of wide_nw
+// wavefronts per node, or (trunk mode 2) lane-group items of kWave/G
+// consecutive nodes of one instance with nx + nu <= 64.
 struct LevelPlan {
     int t;
     int count;

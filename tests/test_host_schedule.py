@@ -124,3 +124,29 @@ def test_autotune_leaves_knobs_without_effect():
         assert not rec["cached"] and rec["knobs"] == [8, 1, 16, 0, 16], rec
         assert st.sweep_autotune(tf, cache=cache, stream=0)["cached"]
     """)
+
+
+def test_stage_lists_are_uploaded_once_and_only_where_read():
+    """Bytes of a schedule's lists (8 a pair, each list rounded to 64)."""
+    hostsim.run("""
+        def bytes_of(tf, knobs=(8, 1, 16, 0, 16)):
+            calls()
+            st.sweep_schedule(tf, knobs)
+            return [int(ln.split()[1]) for ln in calls() if ln.startswith("malloc")]
+
+        p = problem([4] * 5 + [1, 1], 20, 14)           # 341 nodes above 1,024 chains, two to a wavefront
+        tf = factor(p)
+        need = 8 * (341 + 1024 + 512)                   # stages; the panels' chains; the chain wavefronts
+        (got,) = bytes_of(tf)
+        assert need <= got <= need + 64 * 10, (got, need)
+        (got,) = bytes_of(tf, (8, 1, 16, 2, 16))        # form 2: one list for panels, lane groups beside it
+        assert need <= got <= need + 8 * 341 + 64 * 10, (got, need)
+        got, counters = bytes_of(tf, (8, 1, 16, 1, 16))  # form 1: its entry nodes and counters
+        assert need + 8 * 256 <= got <= need + 8 * 256 + 64 * 10 and counters == 4 * (tf.V + 1), (got, counters)
+        # 8 copies in bands: nothing per stage but the panels' list of the first copy
+        q = problem([4] * 5, 4, 2)
+        tf = st.tree_factor_shared(q, 8, stream=0)
+        tf1 = factor(q)
+        (one,), (eight,) = bytes_of(tf1), bytes_of(tf)
+        assert eight <= 8 * (one - 8 * 341) + 8 * 341 + 64 * 80, (one, eight)
+    """)
