@@ -150,3 +150,33 @@ def test_stage_lists_are_uploaded_once_and_only_where_read():
         (one,), (eight,) = bytes_of(tf1), bytes_of(tf)
         assert eight <= 8 * (one - 8 * 341) + 8 * 341 + 64 * 80, (one, eight)
     """)
+
+
+def test_band_shapes_run_in_bands():
+    """The shapes of the GPU tests of banded sweeps take the route those tests are about."""
+    hostsim.run("""
+        from test_gpu_bands import SHAPES, _prob
+        for s in SHAPES:
+            nx, nu, N, S, b0 = s
+            tf = factor(_prob(s))
+            for nrhs in (1, 2):
+                rc, names = sweep(tf, nrhs)
+                banded = nx + nu <= 32 and s[3:] not in ((65, 65), (41, 41))     # too wide; one child too many
+                assert rc == 0 and any(n.startswith("band_kernel") for n in names) == banded, (s, names)
+            tf.free()
+    """)
+
+
+def test_right_hand_sides_per_panel_workgroup():
+    """Launches of 416 nodes or chains and more take all 64 copies in a workgroup, smaller ones 16."""
+    hostsim.run("""
+        for scen in (415, 416):
+            p = treegen.draw_problem(treegen.capped_tree(4, scen, 21), 4, 2, np.random.default_rng(1))
+            tf = st.tree_factor_shared(p, 64, stream=0)
+            calls()
+            rc, names = sweep(tf)
+            got = {n for n in names if "chain64" in n}
+            want = 64 if scen == 416 else 16
+            assert rc == 0 and got == {f"bwd_chain64_kernelILi1ELi{want}EE", f"fwd_chain64_kernelILi1ELi{want}EE"}, names
+            assert {n for n in names if "trunk64" in n} == {"bwd_trunk64_kernelILi1ELi16EE", "fwd_trunk64_kernelILi1ELi16EE"}
+    """)
