@@ -1007,8 +1007,10 @@ int ensure_solver_ws(tree_factors *f, WsNeed need)
         w.bytes = 0;
     }
     // blocks per instance: one per 1024 rows, at most 1024; one per 256 rows (a
-    // row per thread) on handles whose rows then still fit one round of the chip
-    const int per = f->m_tot <= 2048LL * kVB ? kVB : 4 * kVB;
+    // row per thread) on handles of few rows.  20 iterations of NAMA by the second
+    // / by the first: 30,700 rows 6.86 / 7.15 ms, 107,500 7.36 / 7.53, 174,460 6.82 /
+    // 6.87, 245,740 7.62 / 7.37, 488,080 12.10 / 11.91.
+    const int per = f->m_tot <= 768LL * kVB ? kVB : 4 * kVB;
     std::vector<int> blk;
     w.blk_first.assign(f->ninst, 0);
     for (int b = 0; b < f->ninst; ++b) {

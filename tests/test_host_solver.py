@@ -108,3 +108,19 @@ def test_new_handles_need_no_new_pinned_memory():
         round_()
         assert count(calls()) == 2 * 24          # 16 kept
     """)
+
+
+def test_blocks_of_the_vector_passes():
+    """A thread per row up to 196,608 rows in all, then 1,024 rows a block, 1,024 blocks an instance at most."""
+    _run("""
+        for branching, nx, nu, copies in (([2, 2, 2], 4, 2, 1), ([64, 64], 40, 7, 1), ([64, 64], 40, 12, 1), ([16, 16], 20, 10, 40)):
+            p = problem(branching, nx, nu)
+            tf = factor(p) if copies == 1 else factor(*[p] * copies)
+            m = p.m
+            per = 256 if tf.m <= 196608 else 1024
+            log = solve(tf, "nama", 0)
+            grid = {int(ln.split()[3]) for ln in log if "12resid_kernel" in ln}
+            assert grid == {copies * min(1024, -(-m // per))}, (m, grid)
+            tf.free()
+        assert per == 1024 and 256 * 768 == 196608
+    """)
