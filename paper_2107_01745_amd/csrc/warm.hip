@@ -269,9 +269,9 @@ __global__ void adam_kernel(long long n, float *p, const float *g, float *m, flo
 
 struct WarmArgs {
     const InstDesc *inst;
-    const int *sp, *anc;
+    const int *anc;
     const double *cvec, *x0;
-    int din, dout, Nmax;
+    int din, dout;
     float c_scale;
 };
 
@@ -289,7 +289,6 @@ __global__ void features_kernel(WarmArgs a, int ninst, float *X)
 {
     for (int b = blockIdx.y; b < ninst; b += gridDim.y) {
         const InstDesc I = a.inst[b];
-        const int *sp = a.sp + I.sp;
         const int *anc = a.anc + I.sc;  // node-indexed pools share the sc offset
         const double *cv = a.cvec + I.c;
         const Ix total = (Ix)I.V * I.nx;
@@ -314,16 +313,16 @@ template <typename Ix>
 __global__ void scatter_kernel(WarmArgs a, int ninst, const float *Y, double *y, float y_scale)
 {
     for (int b = blockIdx.y; b < ninst; b += gridDim.y) {
-    const InstDesc I = a.inst[b];
-    const Ix W = I.nx + I.nu, nl = (Ix)I.Vnl * W, m = (Ix)I.m;
-    const float *Yb = Y + I.node0 * a.dout;
-    for (Ix k = (Ix)blockIdx.x * blockDim.x + threadIdx.x; k < m; k += (Ix)gridDim.x * blockDim.x) {
-        Ix i, col;
-        if (k < nl) { i = k / W; col = k - i * W; }
-        else { i = (k - nl) / I.nx; col = k - nl - i * I.nx; i += I.Vnl; }
-        const double v = (i == 0 && (int)col < I.nx) ? 0.0 : (double)Yb[(long long)i * a.dout + col] * y_scale;
-        y[I.y + k] = v;
-    }
+        const InstDesc I = a.inst[b];
+        const Ix W = I.nx + I.nu, nl = (Ix)I.Vnl * W, m = (Ix)I.m;
+        const float *Yb = Y + I.node0 * a.dout;
+        for (Ix k = (Ix)blockIdx.x * blockDim.x + threadIdx.x; k < m; k += (Ix)gridDim.x * blockDim.x) {
+            Ix i, col;
+            if (k < nl) { i = k / W; col = k - i * W; }
+            else { i = (k - nl) / I.nx; col = k - nl - i * I.nx; i += I.Vnl; }
+            const double v = (i == 0 && (int)col < I.nx) ? 0.0 : (double)Yb[(long long)i * a.dout + col] * y_scale;
+            y[I.y + k] = v;
+        }
     }
 }
 
@@ -331,21 +330,21 @@ template <typename Ix>
 __global__ void targets_kernel(WarmArgs a, int ninst, const double *y, float *T, float *mask, float inv_scale)
 {
     for (int b = blockIdx.y; b < ninst; b += gridDim.y) {
-    const InstDesc I = a.inst[b];
-    const Ix total = (Ix)I.V * a.dout;
-    float *Tb = T + I.node0 * a.dout, *Mb = mask + I.node0 * a.dout;
-    for (Ix e = (Ix)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (Ix)gridDim.x * blockDim.x) {
-        const int i = (int)(e / a.dout), col = (int)(e - (Ix)i * a.dout);
-        const int w = i < I.Vnl ? I.nx + I.nu : I.nx;
-        float t = 0.0f, mk = 0.0f;
-        if (col < w && !(i == 0 && col < I.nx)) {
-            const long long o = i < I.Vnl ? (long long)i * (I.nx + I.nu) : (long long)I.Vnl * I.nu + (long long)i * I.nx;
-            t = (float)(y[I.y + o + col] * inv_scale);
-            mk = 1.0f;
+        const InstDesc I = a.inst[b];
+        const Ix total = (Ix)I.V * a.dout;
+        float *Tb = T + I.node0 * a.dout, *Mb = mask + I.node0 * a.dout;
+        for (Ix e = (Ix)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (Ix)gridDim.x * blockDim.x) {
+            const int i = (int)(e / a.dout), col = (int)(e - (Ix)i * a.dout);
+            const int w = i < I.Vnl ? I.nx + I.nu : I.nx;
+            float t = 0.0f, mk = 0.0f;
+            if (col < w && !(i == 0 && col < I.nx)) {
+                const long long o = i < I.Vnl ? (long long)i * (I.nx + I.nu) : (long long)I.Vnl * I.nu + (long long)i * I.nx;
+                t = (float)(y[I.y + o + col] * inv_scale);
+                mk = 1.0f;
+            }
+            Tb[e] = t;
+            Mb[e] = mk;
         }
-        Tb[e] = t;
-        Mb[e] = mk;
-    }
     }
 }
 
@@ -360,8 +359,12 @@ void launch_tile(int M, int N, int K, const float *A, int lda, const float *B, i
 }
 
 // Tiles of the row products (C has one row per node row): as wide as the
-// columns, so that the activations are read once; 64 or 128 rows tall where that
-// still gives every compute unit a block, 32 (64 for narrow outputs) below.
+// columns, so that the activations are read once, and 128 rows tall for narrow
+// outputs.  Wider outputs take 32 rows (64 for up to 64 columns) below 32,768 rows
+// and 64 (128) from there, although 64 rows give every compute unit a block from
+// 16,384 on: it takes two to hide the loads.  Network forward by 32 / by 64 rows:
+// 128 units 35.5 / 38.3 us at 16,384 rows, 41.0 / 47.2 at 20,000, 46.1 / 48.3 at
+// 32,767; 160 units 61.3 / 66.3 at 20,000, 85.4 / 79.1 at 32,767.
 // A 65,536-row training step with the wide tile at 64 x 128: 296 us; 128 x 128
 // (three wavefronts per SIMD) 325, 32 x 128 304, 64 x 64 297; 32 reduction rows
 // at a time instead of 16: 328, 8: 348.
@@ -410,14 +413,12 @@ WarmArgs warm_args(const tree_factors *f, const double *x0, float c_scale)
 {
     WarmArgs a{};
     a.inst = f->d_inst;
-    a.sp = f->d_sp;
     a.anc = f->d_anc;
     a.cvec = f->cvec;
     a.x0 = x0;
     const InstDesc &I = f->inst[0];
     a.din = 3 * I.nx + I.N + 1;
     a.dout = I.nx + I.nu;
-    a.Nmax = I.N;
     a.c_scale = c_scale;
     return a;
 }
