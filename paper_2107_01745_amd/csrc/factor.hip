@@ -1218,8 +1218,8 @@ int factor_forest(int count, const tree_desc *trees, const problem_data *datas, 
         STOTREE_HIP(hipMemcpy(f->lo, lo.data(), sizeof(double) * oy, hipMemcpyHostToDevice));
         STOTREE_HIP(hipMemcpy(f->hi, hi.data(), sizeof(double) * oy, hipMemcpyHostToDevice));
     }
-    // raw inputs: concatenated pools (a single instance is uploaded in place)
-    // (raw inputs, work lists and scratch in one temporary allocation)
+    // raw inputs in concatenated pools, work lists and scratch: one temporary
+    // allocation
     struct Part { void *p = nullptr; };
     Part bA, bB, bc, bQ, bR, bS, bq, br, bP, bp, bprob, bscr, berr, braw, bitems;
     DevBuf btmp, bPcal;
@@ -1259,7 +1259,7 @@ int factor_forest(int count, const tree_desc *trees, const problem_data *datas, 
         STOTREE_HIP(hipMalloc(&btmp.p, std::max<size_t>(bytes, 256)));
         for (auto &q : parts) q.first->p = (char *)btmp.p + q.second;
     }
-    auto upload = [&](Part &buf, long long, auto get, auto len) -> int {
+    auto upload = [&](Part &buf, auto get, auto len) -> int {
         long long o = 0;
         for (int b = 0; b < count; ++b) {
             const double *h = get(b);
@@ -1271,17 +1271,17 @@ int factor_forest(int count, const tree_desc *trees, const problem_data *datas, 
         return STOTREE_OK;
     };
 #define NODES(expr) [&](int b) -> long long { const InstDesc &I = f->inst[b]; (void)I; return (expr); }
-    if ((rc = upload(bA, ro.A, [&](int b) { return datas[b].A; }, NODES((long long)I.V * I.nx * I.nx))) ||
-        (rc = upload(bB, ro.B, [&](int b) { return datas[b].B; }, NODES((long long)I.V * I.nx * I.nu))) ||
-        (rc = upload(bc, ro.c, [&](int b) { return datas[b].c; }, NODES((long long)I.V * I.nx))) ||
-        (rc = upload(bQ, ro.Q, [&](int b) { return datas[b].Q; }, NODES((long long)I.Vnl * I.nx * I.nx))) ||
-        (rc = upload(bR, ro.R, [&](int b) { return datas[b].R; }, NODES((long long)I.Vnl * I.nu * I.nu))) ||
-        (anyS && (rc = upload(bS, ro.S, [&](int b) { return datas[b].S; }, NODES((long long)I.Vnl * I.nu * I.nx)))) ||
-        (anyq && (rc = upload(bq, ro.q, [&](int b) { return datas[b].q; }, NODES((long long)I.Vnl * I.nx)))) ||
-        (anyr && (rc = upload(br, ro.r, [&](int b) { return datas[b].r; }, NODES((long long)I.Vnl * I.nu)))) ||
-        (rc = upload(bP, ro.P, [&](int b) { return datas[b].P; }, NODES((long long)(I.V - I.Vnl) * I.nx * I.nx))) ||
-        (anyp && (rc = upload(bp, ro.p, [&](int b) { return datas[b].p; }, NODES((long long)(I.V - I.Vnl) * I.nx))) ) ||
-        (rc = upload(bprob, ro.prob, [&](int b) { return trees[b].prob; }, NODES((long long)I.V))))
+    if ((rc = upload(bA, [&](int b) { return datas[b].A; }, NODES((long long)I.V * I.nx * I.nx))) ||
+        (rc = upload(bB, [&](int b) { return datas[b].B; }, NODES((long long)I.V * I.nx * I.nu))) ||
+        (rc = upload(bc, [&](int b) { return datas[b].c; }, NODES((long long)I.V * I.nx))) ||
+        (rc = upload(bQ, [&](int b) { return datas[b].Q; }, NODES((long long)I.Vnl * I.nx * I.nx))) ||
+        (rc = upload(bR, [&](int b) { return datas[b].R; }, NODES((long long)I.Vnl * I.nu * I.nu))) ||
+        (anyS && (rc = upload(bS, [&](int b) { return datas[b].S; }, NODES((long long)I.Vnl * I.nu * I.nx)))) ||
+        (anyq && (rc = upload(bq, [&](int b) { return datas[b].q; }, NODES((long long)I.Vnl * I.nx)))) ||
+        (anyr && (rc = upload(br, [&](int b) { return datas[b].r; }, NODES((long long)I.Vnl * I.nu)))) ||
+        (rc = upload(bP, [&](int b) { return datas[b].P; }, NODES((long long)(I.V - I.Vnl) * I.nx * I.nx))) ||
+        (anyp && (rc = upload(bp, [&](int b) { return datas[b].p; }, NODES((long long)(I.V - I.Vnl) * I.nx))) ) ||
+        (rc = upload(bprob, [&](int b) { return trees[b].prob; }, NODES((long long)I.V))))
         return rc;
 #undef NODES
     STOTREE_HIP(hipMalloc(&bPcal.p, sizeof(double) * (size_t)std::max(1LL, ro.Pcal)));

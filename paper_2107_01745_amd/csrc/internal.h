@@ -256,7 +256,6 @@ int dual_grad_noalloc_impl(const tree_factors *f, const double *x0, const double
 
 // bands.hip
 std::vector<int> band_cuts(const InstDesc &I, const int *sp, const int *cp, int last);
-struct ListArena;
 void build_bands(tree_factors *f, const std::vector<std::vector<int>> &cuts, ListArena &arena);
 // pass 0: backward, 1: forward, 2: both (band 0)
 void launch_band(const tree_factors *f, const SweepArgs &a, int nrhs, int band, int pass, hipStream_t st);

@@ -10,14 +10,15 @@
 // k_i = -R~_i^{-1} g_i, qhat_i = chat_i + s_i y_i^x + sum_j A_j' qhat_j +
 // K_i' g_i; forward u_i = K_i x_i + k_i, x_j = A_j x_i + B_j u_i + c_j.
 //
-// Mapping.  One workgroup of four wavefronts per node (per chain below s*).
-// The input panel of a product (qhat, g or [x; u] of all 64 right-hand
-// sides, one LDS row per vector entry) sits in LDS; the factor operand is read
-// straight from HBM in the layout the single-vector sweep streams.  The output
-// of a product is cut into 16-row tiles of the x part and of the u part, each
-// tile in two halves of 32 right-hand sides; the (tile, half) tasks are dealt
-// round-robin to the wavefronts, and every task keeps its two 16x16 result
-// blocks in registers.  The result accumulators start at the node's own
+// Mapping.  One workgroup of four wavefronts per node (per chain below s*)
+// for all 64 right-hand sides, or four of them for 16 each where a launch has
+// few nodes.  The input panel of a product (qhat, g or [x; u] of the
+// workgroup's right-hand sides, one LDS row per vector entry) sits in LDS; the
+// factor operand is read straight from HBM in the layout the single-vector
+// sweep streams.  The output of a product is cut into 16-row tiles of the x part
+// and of the u part, each tile in two halves of 32 right-hand sides (one task
+// of 16 in the groups of 16); the tasks are dealt round-robin to the wavefronts,
+// and every task keeps its two (one) 16x16 result blocks in registers.  The result accumulators start at the node's own
 // vector terms (s_i y_i + chat_i / sig_i backward, k_i and c_j forward); the
 // finished blocks go to the LDS panel, where they are the input of the next
 // product (g for [K; -R~^{-1}] g, [x; u] for the children), and each lane
