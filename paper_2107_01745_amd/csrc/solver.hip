@@ -1455,15 +1455,17 @@ int solve(const tree_factors *fc, const double *x0, const solver_opts *opts_in, 
     // otherwise).  Instances finish at the residual, in the middle of an
     // iteration, so the count is requested there and the host waits with the rest
     // of the iteration queued behind it; a solve that ends has queued no launch for
-    // the poll.  GPAD has only two short kernels behind its residual: from its
-    // second poll on, one more iteration goes in before the host waits (whose
-    // kernels find every instance finished if the count ends the solve).
+    // the poll.  One whole iteration more goes in before the host waits where that
+    // cannot be in vain, in a solve without a residual to stop at (eps = 0: it runs
+    // to max_iter; 0.5 to 3% on trees swept in bands), and for GPAD, which has only
+    // two short kernels behind its residual, from the second poll on (if the count
+    // then ends the solve, those kernels find every instance finished).
     // Accepted at the first residual, against always queueing one more: MINFBE on
     // the 6,485-node tree with nx=50, nu=30 588 us (660), on the 4,095-node
     // two-mode tree 197 (237), GPAD there 183 (195); 20 iterations of NAMA on an
-    // 8-scenario tree with nx=4, nu=2 1,612 (1,559), elsewhere the same.
+    // 8-scenario tree with nx=4, nu=2 and eps > 0 1,612 (1,559), elsewhere the same.
     while (ndone < f->ninst && k <= last) {
-        const bool inside = method != 2 || polls == 0;
+        const bool inside = o.eps > 0.0 && (method != 2 || polls == 0);
         hipError_t e = hipSuccess;
         for (int c = ahead; c < o.check_every && k <= last && e == hipSuccess; ++c)
             e = enqueue(inside && (c + 1 == o.check_every || k == last));

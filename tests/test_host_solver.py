@@ -17,10 +17,10 @@ SETUP = """
     fake.fake_on_launch(on_launch)
     SOLVERS = dict(nama=L.nama_solve, minfbe=L.minfbe_solve, gpad=L.gpad_solve)
 
-    def solve(tf, method, stop, check_every=1, max_iter=1000):
+    def solve(tf, method, stop, check_every=1, max_iter=1000, eps=1e-6):
         state.update(seen=0, stop=stop, ninst=tf.ninst)
         info = st.SolverInfo()
-        opts = st.make_opts(lam=0.1, eps=1e-6, max_iter=max_iter, check_every=check_every, div_window=-1)
+        opts = st.make_opts(lam=0.1, eps=eps, max_iter=max_iter, check_every=check_every, div_window=-1)
         calls()
         rc = SOLVERS[method](tf.handle, buf(tf.x0_len), C.byref(opts), buf(tf.m), buf(tf.x_len), buf(tf.u_len),
                              C.byref(info), None)
@@ -123,4 +123,18 @@ def test_blocks_of_the_vector_passes():
             assert grid == {copies * min(1024, -(-m // per))}, (m, grid)
             tf.free()
         assert per == 1024 and 256 * 768 == 196608
+    """)
+
+
+def test_a_solve_without_a_residual_to_stop_at_keeps_one_iteration_ahead():
+    """eps = 0: the host waits for the count of one iteration with the whole next one queued, and never
+    queues more than max_iter asks for."""
+    _run("""
+        tf = factor(problem([2, 2, 2], 4, 2))
+        for method in SOLVERS:
+            log = solve(tf, method, 10 ** 9, max_iter=6, eps=0.0)
+            assert state["seen"] == 7
+            waits = [k for k, ln in enumerate(log) if ln == "event sync"]
+            resid = lambda part: sum("fin_resid_kernel" in ln for ln in part)
+            assert [resid(log[:w]) for w in waits] == [2, 3, 4, 5, 6, 7], method
     """)
