@@ -702,7 +702,9 @@ int chain_group(int ldM, int group_min)
 // all.  The bands save launches and latency, not bandwidth: per sweep against
 // one launch per stage (MI355X) 16 us against 46 on the 8-scenario tree with
 // nx=4, nu=2; 62 against 134 on the 4,095-node two-mode tree with nx=10, nu=4;
-// 76 against 91 on 2,000 scenarios of 6 stages with nx=20, nu=10.
+// 76 against 91 on 2,000 scenarios of 6 stages with nx=20, nu=10; near the limit
+// below 97 against 119 on 8,000 scenarios of those 6 stages, 325 against 342 on
+// 15, 88 against 180 on 8,192 scenarios of 13 stages with nx=10, nu=4.
 // Wider blocks lose (nx=40, nu=20: 180 us against 140: a lane group's rows are
 // then one long serial product), and so does a handle where wide instances
 // need the per-stage launches anyway.

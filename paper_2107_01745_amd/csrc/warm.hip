@@ -450,6 +450,7 @@ int mlp_forward_impl(int rows, int din, int dh, int dout, const float *P, const 
     return launch_rows<false>(rows, dout, dh, H2, dh, P + L.W3, dout, Y, dout, P + L.b3, 0, nullptr, 0, st);
 }
 
+// (rows floats of it are spare: the length is part of the interface)
 long long mlp_work_len(int rows, int din, int dh, int dout)
 {
     const long long slices = (rows + kSliceRows - 1) / kSliceRows;
